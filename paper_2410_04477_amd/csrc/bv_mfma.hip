@@ -136,7 +136,7 @@ bv_mfma_kernel(AdjArgs a, ThetaPack thp) {
         const T dx = su[i] - sj0;
         const T dy = su[P + i] - sj1;
         const T dz = su[2 * P + i] - sj2;
-        const T x = sqrt_fast<T>(dx * dx + dy * dy + dz * dz);
+        const T x = distance<T>(dx, dy, dz);
         T v = sig2 * mc.rho(x) + ((i == j) ? nug : T(0));
         if (!(i < p && j < p)) v = (i == p && j < p) ? yb : ((i == j) ? T(1) : T(0));
         acc[s][r] = tJ[s] < G ? v : T(0);
@@ -417,7 +417,7 @@ bv_mfma_kernel(AdjArgs a, ThetaPack thp) {
             const T dx = su[i] - su[j];
             const T dy = su[P + i] - su[P + j];
             const T dz = su[2 * P + i] - su[2 * P + j];
-            const T x = sqrt_fast<T>(dx * dx + dy * dy + dz * dz);
+            const T x = distance<T>(dx, dy, dz);
             T rho, drho;
             mc.rho_drange(x, irange, rho, drho);
             const double wv2 = wgt * (double)c[r];

@@ -1,13 +1,15 @@
-// One-wave matrix-core kernels, FP64 instantiations (the kernel is in wave_kernel.hpp).
+// One-wave matrix-core kernels, FP64 instantiations of the value and of the
+// two-launch gradient (the kernel is in wave_kernel.hpp; the one-launch gradient
+// and the prediction are in sources of their own, so that they compile side by side).
 #include "wave_kernel.hpp"
 
 namespace bv {
 
 hipError_t launch_wave_f64(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s) {
   if (mode == 0) return launch_wave_t<double, 0>(g, a, thp, grid, s);
-  if (mode == 1) return launch_wave_t<double, 1>(g, a, thp, grid, s);
-  if (mode == 5) return launch_wave_t<double, 5>(g, a, thp, grid, s);
-  if (mode == 4) return launch_wave_t<double, 4>(g, a, thp, grid, s);
+  if (mode == 1) return launch_wave_f64_tiles(g, a, thp, grid, s);
+  if (mode == 5) return launch_wave_f64_grad(g, a, thp, grid, s);
+  if (mode == 4) return launch_wave_f64_pred(g, a, thp, grid, s);
   if (mode == 6) return launch_wave_t<double, 6>(g, a, thp, grid, s);
   if (mode == 3) return launch_wave_t<double, 3>(g, a, thp, grid, s);
   return hipErrorInvalidValue;

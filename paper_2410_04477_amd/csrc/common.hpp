@@ -112,7 +112,7 @@ __device__ inline void bessel_k_pair_quad(double x, double mu, double& k_mu, dou
 // g / range.  Not inlined: its loops would otherwise be copied into every
 // generation site.
 __device__ __noinline__ inline void matern_general(double x, const BesselOrder& o, double* rho, double* g) {
-  if (!(x > 0.0)) {
+  if (!(x > 1e-140)) {   // a coincident pair (distance<double> gives 1e-150)
     *rho = 1.0;
     *g = 0.0;
     return;
@@ -151,7 +151,7 @@ __device__ __noinline__ inline void matern_general(double x, const BesselOrder& 
 // psi(nu)) + D_nu].
 __device__ __noinline__ inline void matern_general_dnu(double x, const BesselOrder& o, double* rho, double* g,
                                                        double* drho_dnu) {
-  if (!(x > 0.0)) {
+  if (!(x > 1e-140)) {   // a coincident pair (distance<double> gives 1e-150)
     *rho = 1.0;
     *g = 0.0;
     *drho_dnu = 0.0;
@@ -211,9 +211,30 @@ template <typename T> __device__ __forceinline__ T expneg(T x);
 template <> __device__ __forceinline__ double expneg<double>(double x) { return exp(-x); }
 template <> __device__ __forceinline__ float expneg<float>(float x) { return __expf(-x); }
 
-// 2^-x: one v_exp_f32 in FP32
+// 2^-x.  FP32: one v_exp_f32.  FP64, x >= 0: 2^-x = 2^m 2^f with m = -x rounded
+// to an integer and f = -x - m exact, |f| <= 1/2, and 2^f = 1 + f q(f), q the
+// degree-10 interpolant of (2^f - 1) / f at the Chebyshev nodes (8.4e-18
+// relative; with rounding 1.35e-16 at most and 3.8e-17 in the mean over
+// x in [1e-10, 1e3], as the library's exp2): 16 instructions.  A NaN or infinite
+// x gives NaN.
 template <typename T> __device__ __forceinline__ T exp2neg(T x);
-template <> __device__ __forceinline__ double exp2neg<double>(double x) { return exp2(-x); }
+template <> __device__ __forceinline__ double exp2neg<double>(double x) {
+  const double m = __builtin_rint(-x);
+  const double f = -x - m;
+  double q = 0x1.e9d3fe3952179p-32;
+  q = __builtin_fma(q, f, 0x1.e6063f7217bc6p-28);
+  q = __builtin_fma(q, f, 0x1.b524fae627834p-24);
+  q = __builtin_fma(q, f, 0x1.62bfd47773353p-20);
+  q = __builtin_fma(q, f, 0x1.ffcbfc670dcd4p-17);
+  q = __builtin_fma(q, f, 0x1.430913096fd9fp-13);
+  q = __builtin_fma(q, f, 0x1.5d87fe78a5276p-10);
+  q = __builtin_fma(q, f, 0x1.3b2ab6fba1ddap-7);
+  q = __builtin_fma(q, f, 0x1.c6b08d704a0c2p-5);
+  q = __builtin_fma(q, f, 0x1.ebfbdff82c598p-3);
+  q = __builtin_fma(q, f, 0x1.62e42fefa39efp-1);
+  q = __builtin_fma(q, f, 1.0);
+  return __builtin_amdgcn_ldexp(q, (int)m);
+}
 template <> __device__ __forceinline__ float exp2neg<float>(float x) { return __builtin_amdgcn_exp2f(-x); }
 
 template <typename T> __device__ __forceinline__ T sqrt_(T x);
@@ -251,20 +272,13 @@ struct MaternCoef {
   __device__ __forceinline__ T drange(T x, T inv_range) const {
     return x * inv_range * expneg<T>(x) * (g0 + x * (g1 + g2 * x));
   }
-  // -(sigma2 rho(x)) with the scale and sign folded into the coefficients
-  // (s0, s1, s2) = -sigma2 (1, c1, c2)
-  __device__ __forceinline__ T neg_cov(T x, T s0, T s1, T s2) const { return expneg<T>(x) * (s0 + x * (s1 + s2 * x)); }
-  // d rho / d range with 1 / range folded into (h0, h1, h2) = (g0, g1, g2) / range
-  __device__ __forceinline__ T drange_scaled(T x, T h0, T h1, T h2) const {
-    return x * expneg<T>(x) * (h0 + x * (h1 + h2 * x));
-  }
-  // the two above for a distance u = x log2(e) (e^-x = 2^-u), the coefficients
-  // of u^k carrying the factor ln(2)^k (neg_cov) or ln(2)^(k+1) (drange)
-  __device__ __forceinline__ T neg_cov_log2(T u, T s0, T s1, T s2) const {
-    return exp2neg<T>(u) * (s0 + u * (s1 + s2 * u));
-  }
-  __device__ __forceinline__ T drange_scaled_log2(T u, T h0, T h1, T h2) const {
-    return u * exp2neg<T>(u) * (h0 + u * (h1 + h2 * u));
+  // -(sigma2 rho) and d rho / d range for a distance u = x log2(e) and e = 2^-u = e^-x
+  // with the scales and sign in the coefficients: (s0, s1, s2) =
+  // -sigma2 (1, c1 ln 2, c2 ln(2)^2), (h0, h1, h2) = (g0 ln 2, g1 ln(2)^2,
+  // g2 ln(2)^3) / range
+  static __device__ __forceinline__ T neg_cov_log2(T u, T e, T s0, T s1, T s2) { return e * (s0 + u * (s1 + s2 * u)); }
+  static __device__ __forceinline__ T drange_log2(T u, T e, T h0, T h1, T h2) {
+    return u * e * (h0 + u * (h1 + h2 * u));
   }
 };
 
@@ -302,9 +316,86 @@ template <typename T> struct MaternF<T, true> {
   }
 };
 
-template <typename T> __device__ __forceinline__ T sqrt_fast(T x);
-template <> __device__ __forceinline__ double sqrt_fast<double>(double x) { return sqrt(x); }
-template <> __device__ __forceinline__ float sqrt_fast<float>(float x) { return __builtin_amdgcn_sqrtf(x); }
+// 1 / sqrt(x) in FP64, 0 < x < inf normal: the hardware estimate y (2^-24) and one
+// third-order step, y + y e (1/2 + 3/8 e) with e = 1 - x y^2: 1.4e-16 relative
+// at most (1 / sqrt(x) through the library: 1.7e-16), 5 dependent operations
+// instead of about 20.
+__device__ __forceinline__ double rsqrt_fast(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = __builtin_fma(-(x * y), y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+
+// Distance sqrt(dx^2 + dy^2 + dz^2).  FP64: from the estimate of 1 / sqrt in one
+// third-order step as above; the sum starts from 1e-300, so coincident points
+// come out at 1e-150 instead of 0 * inf.
+template <typename T> __device__ __forceinline__ T distance(T dx, T dy, T dz);
+template <> __device__ __forceinline__ double distance<double>(double dx, double dy, double dz) {
+  const double x = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, 1e-300)));
+  const double y = __builtin_amdgcn_rsq(x);
+  const double g = x * y;
+  const double e = __builtin_fma(-g, y, 1.0);
+  return __builtin_fma(g * e, __builtin_fma(e, 0.375, 0.5), g);
+}
+template <> __device__ __forceinline__ float distance<float>(float dx, float dy, float dz) {
+  return __builtin_amdgcn_sqrtf(dx * dx + dy * dy + dz * dz);
+}
+
+// distance() and exp2neg() of four pairs.  STAGED (FP64): step by step across the
+// four.  A dependent FP64 operation waits about 8 cycles and issues in 4, and the
+// scheduler left to itself runs the pairs one after the other, so the kernels
+// that hold one wave per SIMD would wait half of the time.
+template <bool STAGED>
+__device__ __forceinline__ void distance_exp2neg4(const double (&dx)[4], const double (&dy)[4], const double (&dz)[4],
+                                                  double (&u)[4], double (&w)[4]) {
+  if constexpr (!STAGED) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      u[r] = distance<double>(dx[r], dy[r], dz[r]);
+      w[r] = exp2neg<double>(u[r]);
+    }
+    return;
+  }
+#define BV_STEP(...)                             \
+  do {                                           \
+    _Pragma("unroll") for (int r = 0; r < 4; ++r) { __VA_ARGS__; } \
+    __builtin_amdgcn_sched_barrier(0);           \
+  } while (0)
+  double y[4], e[4], t[4], m[4];
+  BV_STEP(u[r] = __builtin_fma(dz[r], dz[r], 1e-300));
+  BV_STEP(u[r] = __builtin_fma(dy[r], dy[r], u[r]));
+  BV_STEP(u[r] = __builtin_fma(dx[r], dx[r], u[r]));
+  BV_STEP(y[r] = __builtin_amdgcn_rsq(u[r]));
+  BV_STEP(u[r] = u[r] * y[r]);
+  BV_STEP(e[r] = __builtin_fma(-u[r], y[r], 1.0));
+  BV_STEP(t[r] = __builtin_fma(e[r], 0.375, 0.5));
+  BV_STEP(e[r] = u[r] * e[r]);
+  BV_STEP(u[r] = __builtin_fma(e[r], t[r], u[r]));
+  BV_STEP(m[r] = __builtin_rint(-u[r]));
+  BV_STEP(y[r] = -u[r] - m[r]);
+  BV_STEP(w[r] = __builtin_fma(0x1.e9d3fe3952179p-32, y[r], 0x1.e6063f7217bc6p-28));
+  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.b524fae627834p-24));
+  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.62bfd47773353p-20));
+  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.ffcbfc670dcd4p-17));
+  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.430913096fd9fp-13));
+  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.5d87fe78a5276p-10));
+  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.3b2ab6fba1ddap-7));
+  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.c6b08d704a0c2p-5));
+  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.ebfbdff82c598p-3));
+  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.62e42fefa39efp-1));
+  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 1.0));
+  BV_STEP(w[r] = __builtin_amdgcn_ldexp(w[r], (int)m[r]));
+#undef BV_STEP
+}
+template <bool STAGED>
+__device__ __forceinline__ void distance_exp2neg4(const float (&dx)[4], const float (&dy)[4], const float (&dz)[4],
+                                                  float (&u)[4], float (&w)[4]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    u[r] = distance<float>(dx[r], dy[r], dz[r]);
+    w[r] = exp2neg<float>(u[r]);
+  }
+}
 
 // rho and x * d rho / d x * (-1) / range, i.e. d rho(h/range) / d range.
 template <typename T>

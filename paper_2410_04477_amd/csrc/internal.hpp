@@ -107,6 +107,9 @@ inline bool wave_regadj(int g, bool fp32, int lmax) {
 __host__ __device__ constexpr int pred_rows(int m) { return (m + 3) & ~3; }
 hipError_t launch_wave_f32(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
 hipError_t launch_wave_f64(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
+hipError_t launch_wave_f64_grad(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);    // mode 5
+hipError_t launch_wave_f64_pred(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);    // mode 4
+hipError_t launch_wave_f64_tiles(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);   // mode 1
 hipError_t launch_wave_gen_f32(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
 hipError_t launch_wave_gen_f64(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
 // dispatches on a.gen to the closed-form or the Bessel-form kernels

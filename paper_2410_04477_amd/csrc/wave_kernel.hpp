@@ -12,9 +12,17 @@
 // the lanes holding its columns write them to LDS; every lane factors the
 // 4 x 4 diagonal block (all lanes compute the same values in lockstep, so the
 // redundancy costs nothing); each lane solves up to ceil((P - 16 K) / 64)
-// panel rows (the TRSM / TRSV of Alg. 1; the border row becomes
+// panel rows, or in FP64 forms the entries that its matrix-core operands need
+// (the TRSM / TRSV of Alg. 1; the border row becomes
 // w = L^-1 y_J); the trailing tiles take one rank-4 MFMA each (the Schur
-// update).  Lanes exchange panel data through LDS with wavefront-scope
+// update).  What bounds it: matrix-core and vector operations of FP32 and FP64
+// share the same units on gfx950 (a wave that alternates them takes the sum of
+// their times), so a block costs its MFMA time plus its vector instructions,
+// and at one wave per SIMD every wait as well.  FP64, n = 1e6, m = 120: value
+// 4.68 -> 3.73 ms, prediction of 1e5 points 1.12 -> 0.78 ms; n = 1e5, m = 60:
+// value and gradient 761 -> 496 us (square root, exponential and 1 / sqrt in a
+// third-order step from the hardware estimates, masks only in the edge tiles,
+// row panels, two waves per SIMD up to G = 5 or 6).  Lanes exchange panel data through LDS with wavefront-scope
 // fences, so a panel costs no cross-wave synchronisation.  Pivots d_k and
 // border entries w_k (k >= m) give log det and the quadratic form, summed in
 // FP64.
@@ -83,7 +91,7 @@ template <> struct WMma<double> {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
   static __device__ __forceinline__ constexpr int row(int g, int r) { return g + 4 * r; }
-  static __device__ __forceinline__ double rsqrt(double x) { return 1.0 / sqrt(x); }
+  static __device__ __forceinline__ double rsqrt(double x) { return rsqrt_fast(x); }
   static __device__ __forceinline__ constexpr int aop(int l, int s) { return l * 4 + s; }
   static __device__ __forceinline__ constexpr int at(int i, int j) { return (j + 16 * (i & 3)) * 4 + (i >> 2); }
 };
@@ -124,8 +132,25 @@ __host__ __device__ constexpr int wave_lds_elems(int G, int mode) {
          (mode == 5 ? 16 * G : 0);
 }
 
-template <typename T, int G, int MODE>
-constexpr int wave_min_waves() { return (sizeof(T) == 4 && (G <= 9 || MODE == 3)) || MODE == 6 ? 2 : 1; }
+// Waves per SIMD that a kernel's registers have to allow (512 per lane and SIMD).
+// A wave's matrix-core and vector instructions share the FP32 / FP64 units (one
+// wave that mixes them takes the sum of their times), so more waves only hide
+// latency; two already do, and the first bound below that keeps every tile in
+// registers is taken.  FP64 (8 registers a tile and lane): value and prediction
+// kernels 4, 3 and 2 waves up to G = 2, 4, 6; the one-launch gradient, whose
+// contraction holds more beside the tiles, 2 up to G = 5 (n = 1e5, m = 60 value and
+// gradient: 631 us with one wave per SIMD).  FP32: 5 up to G = 5 (96 registers).
+template <typename T, int G, int MODE, bool GEN>
+constexpr int wave_min_waves() {
+  if (MODE == 6) return 2;
+  if (sizeof(T) == 8) {
+    if (GEN || MODE == 1 || MODE == 3) return 1;
+    if (MODE == 5) return G <= 5 ? 2 : 1;
+    return G <= 2 ? 4 : G <= 4 ? 3 : G <= 6 ? 2 : 1;
+  }
+  if (MODE == 0 && G <= 5) return 5;
+  return G <= 9 || MODE == 3 ? 2 : 1;
+}
 
 // Modes: 0 value; 1 value and gradient in one launch; 2 value and the factor
 // tiles to the tile buffer; 3 gradient from those tiles (a second launch that
@@ -145,16 +170,22 @@ constexpr int wave_min_waves() { return (sizeof(T) == 4 && (G <= 9 || MODE == 3)
 // exceed the register file); mode 3 takes the adjoint from its tiles.
 // GEN: covariances by the Bessel form for any nu instead of the closed forms.
 template <typename T, int G, int MODE, bool GEN>
-__global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_kernel(AdjArgs a, ThetaPack thp) {
+__global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wave_kernel(AdjArgs a, ThetaPack thp) {
   constexpr int P = 16 * G;
   constexpr int NT = G * (G + 1) / 2;
   typedef WMma<T> M;
   typedef typename M::acc acc_t;
   extern __shared__ __align__(16) unsigned char smem[];
   T* su = reinterpret_cast<T*>(smem);  // scaled coordinates relative to the block's first point, su[k * P + i]
-  // FP32 closed forms: the coordinates carry a factor log2(e), so e^-x is one
-  // exp2 of the distance and the polynomial coefficients carry powers of ln 2
-  constexpr bool LOG2U = !GEN && sizeof(T) == 4;
+  // closed forms: the coordinates carry a factor log2(e), so e^-x is the exp2 of
+  // the distance (one instruction in FP32, no argument reduction by ln 2 in FP64)
+  // and the polynomial coefficients carry powers of ln 2
+  constexpr double UNIT = GEN ? 1.0 : kLog2E;
+  // The FP64 gradient at G = 9 (45 tiles, 360 registers, with the right-hand sides'
+  // working set) fits the registers without scratch only with masks instead of
+  // branches in the generation, the panel kept by columns and one nest of updates.
+  constexpr bool TIGHT = sizeof(T) == 8 && MODE == 5 && G == 9;
+  constexpr bool STAGED = wave_min_waves<T, G, MODE, GEN>() == 1;
   T* work = su + 3 * P;
   // MODE 5 appends 16 rows to the panel (the identity rows whose elimination
   // gives the inverse of each diagonal tile of the factor)
@@ -187,7 +218,10 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
   const int mq = MODE == 4 ? pred_rows(m) : m;
   const int p = mq + l;
   // rows that hold a point (the rest of the P rows are identity padding)
-  auto real_row = [&](int i) __attribute__((always_inline)) { return i < p && (MODE != 4 || i < m || i >= mq); };
+  // (no short circuits: as branches they made the compiler drop a mask of gen_tile)
+  auto real_row = [&](int i) __attribute__((always_inline)) {
+    return (int)(i < p) & ((int)(MODE != 4) | (int)(i < m) | (int)(i >= mq));
+  };
   if (MODE == 4 && l == 0) return;
   const double* org = (MODE == 4 ? a.locs2 : a.locs) + (size_t)b0 * a.d;   // coordinate origin: the block's first point
 
@@ -203,8 +237,11 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
         src = a.locs + (size_t)g * a.d;
         if (MODE != 3) sy[i] = T(a.y[g]);
       }
-      for (int k = 0; k < 3; ++k)
-        su[k * P + i] = k < a.d ? T((src[k] - org[k]) * (th.inv_scale[k] * (LOG2U ? kLog2E : 1.0))) : T(0);
+      for (int k = 0; k < 3; ++k) {
+        T v = k < a.d ? T((src[k] - org[k]) * (th.inv_scale[k] * UNIT)) : T(0);
+        if constexpr (sizeof(T) == 8) v = v > 1e140 ? 1e140 : v < -1e140 ? -1e140 : v;   // squares stay finite
+        su[k * P + i] = v;
+      }
     } else {
       if (MODE != 3) sy[i] = T(0);
       for (int k = 0; k < 3; ++k) su[k * P + i] = T(0);
@@ -228,13 +265,12 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
   // the coefficients
   T ns0 = T(0), ns1 = T(0), ns2 = T(0);
   if constexpr (!GEN) {
-    const double u1 = LOG2U ? kLn2 : 1.0;
     ns0 = -sig2;
-    ns1 = T(-th.sigma2 * (double)mc.c1 * u1);
-    ns2 = T(-th.sigma2 * (double)mc.c2 * u1 * u1);
+    ns1 = T(-th.sigma2 * (double)mc.c1 * kLn2);
+    ns2 = T(-th.sigma2 * (double)mc.c2 * kLn2 * kLn2);
   }
-  // mode 6: tile row I's coordinates (row M::row(lg, r) of the tile in ri[r])
-  // and the generation of one tile, as in the loop below
+  // tile row I's coordinates (row M::row(lg, r) of the tile in ri[r]) and the
+  // generation of one tile
   auto row_coords = [&](int I, T (&ri)[4][3]) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -248,74 +284,59 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
     constexpr int I = decltype(I_c)::value, J = decltype(J_c)::value;
     const int j = J * 16 + lr;
     const T sj0 = su[j], sj1 = su[P + j], sj2 = su[2 * P + j];
+    T dx[4], dy[4], dz[4], u[4], e[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int i = I * 16 + M::row(lg, r);
-      const T dx = ri[r][0] - sj0, dy = ri[r][1] - sj1, dz = ri[r][2] - sj2;
-      const T x = sqrt_fast<T>(dx * dx + dy * dy + dz * dz);
+      dx[r] = ri[r][0] - sj0;
+      dy[r] = ri[r][1] - sj1;
+      dz[r] = ri[r][2] - sj2;
+    }
+    if constexpr (!GEN) distance_exp2neg4<STAGED>(dx, dy, dz, u, e);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
       // the tiles hold the negated matrix (updates add L L^T)
       T v;
-      if constexpr (GEN) v = -(sig2 * mc.rho(x));
-      else if constexpr (LOG2U) v = mc.neg_cov_log2(x, ns0, ns1, ns2);
-      else v = mc.neg_cov(x, ns0, ns1, ns2);
-      if constexpr (I == J) v -= (i == j) ? nug : T(0);   // the nugget: same-index pairs only
-      if (!(real_row(i) && real_row(j))) v = (i == j) ? T(-1) : T(0);
+      if constexpr (GEN) v = -(sig2 * mc.rho(distance<T>(dx[r], dy[r], dz[r])));
+      else v = mc.neg_cov_log2(u[r], e[r], ns0, ns1, ns2);
+      if constexpr (I == J) v -= (M::row(lg, r) == lr) ? nug : T(0);   // the nugget: same-index pairs only
       acc[tix(I, J)][r] = v;
     }
-    if (I == (p >> 4)) {  // border row p: y_J
-      const T yb = sy[j];
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (I * 16 + M::row(lg, r) == p && j < p) acc[tix(I, J)][r] = -yb;
-    }
-    // D = 0 * 0 + C: hands the finished tile to the accumulator registers now,
-    // so the generated values do not pile up in VGPRs until the first update
-    // (the FP32 gradient kernels up to G = 9 keep the tiles in VGPRs and skip it)
-    if constexpr (!(sizeof(T) == 4 && G <= 9 && (MODE == 5 || MODE == 2)))
-      acc[tix(I, J)] = M::op(T(0), T(0), acc[tix(I, J)]);
-  };
-  if constexpr (!LEFT) {   // the whole matrix now (mode 6: a tile column at a time, through gen_tile)
-  static_for<0, G>(BV_CI(I) {
-    BV_CV(I);
-    T ri[4][3];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = I * 16 + M::row(lg, r);
-      ri[r][0] = su[i];
-      ri[r][1] = su[P + i];
-      ri[r][2] = su[2 * P + i];
-    }
-    static_for<0, I + 1>(BV_CI(J) {
-      BV_CV(J);
-      const int j = J * 16 + lr;
-      const T sj0 = su[j], sj1 = su[P + j], sj2 = su[2 * P + j];
+    // Rows and columns that hold no point: only the tile rows from p on (and,
+    // for prediction, the tiles of the padding between neighbours and block)
+    // have any, so the others skip the masks (a wave-uniform branch).
+    if (TIGHT || I >= (p >> 4) || (MODE == 4 && (I == (m >> 4) || J == (m >> 4)))) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int i = I * 16 + M::row(lg, r);
-        const T dx = ri[r][0] - sj0, dy = ri[r][1] - sj1, dz = ri[r][2] - sj2;
-        const T x = sqrt_fast<T>(dx * dx + dy * dy + dz * dz);
-        // the tiles hold the negated matrix (updates add L L^T)
-        T v;
-        if constexpr (GEN) v = -(sig2 * mc.rho(x));
-        else if constexpr (LOG2U) v = mc.neg_cov_log2(x, ns0, ns1, ns2);
-        else v = mc.neg_cov(x, ns0, ns1, ns2);
-        if constexpr (I == J) v -= (i == j) ? nug : T(0);   // the nugget: same-index pairs only
-        if (!(real_row(i) && real_row(j))) v = (i == j) ? T(-1) : T(0);
-        acc[tix(I, J)][r] = v;
+        const T v = acc[tix(I, J)][r];
+        acc[tix(I, J)][r] = real_row(i) & real_row(j) ? v : (i == j) ? T(-1) : T(0);
       }
       if (I == (p >> 4)) {  // border row p: y_J
         const T yb = sy[j];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (I * 16 + M::row(lg, r) == p && j < p) acc[tix(I, J)][r] = -yb;
+        for (int r = 0; r < 4; ++r) {
+          const T v = acc[tix(I, J)][r];
+          acc[tix(I, J)][r] = (int)(I * 16 + M::row(lg, r) == p) & (int)(j < p) ? -yb : v;
+        }
       }
-      // D = 0 * 0 + C: hands the finished tile to the accumulator registers now,
-      // so the generated values do not pile up in VGPRs until the first update
-      // (the FP32 gradient kernels up to G = 9 keep the tiles in VGPRs and skip it)
-      if constexpr (!(sizeof(T) == 4 && G <= 9 && (MODE == 5 || MODE == 2)))
-        acc[tix(I, J)] = M::op(T(0), T(0), acc[tix(I, J)]);
+    }
+    // Where the tiles outgrow the VGPRs the finished tile goes to the accumulator
+    // registers now, so that the generated values do not pile up until the first
+    // update: by D = 0 * 0 + C, or (the FP64 value kernels, whose first 32 tiles
+    // fill the accumulator registers) by asking for the move itself.
+    constexpr bool ONE = sizeof(T) == 8 && wave_min_waves<T, G, MODE, GEN>() == 1;
+    if constexpr (ONE && MODE == 0) {
+      if constexpr (tix(I, J) < 32) asm volatile("" : "+a"(acc[tix(I, J)]));
+    } else if constexpr (sizeof(T) == 8 ? ONE || (LEFT && G == 10) : !(G <= 9 && (MODE == 5 || MODE == 2))) {
+      acc[tix(I, J)] = M::op(T(0), T(0), acc[tix(I, J)]);
+    }
+  };
+  if constexpr (!LEFT) {   // the whole matrix now (mode 6: a tile column at a time)
+    static_for<0, G>(BV_CI(I) {
+      T ri[4][3];
+      row_coords(decltype(I_c)::value, ri);
+      static_for<0, decltype(I_c)::value + 1>(BV_CI(J) { gen_tile(I_c, J_c, ri); });
     });
-  });
   }
 
   // ---- factorisation, four columns per step -----------------------------------
@@ -345,7 +366,8 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
   // the panel at column k0: 4 x 4 diagonal block (same values in every lane),
   // then its rows from the diagonal tile down (zero above the block, L_dd in
   // it, TRSM below); pivots and border entries to LDS
-  auto factor_panel = [&](int k0) __attribute__((always_inline)) {
+  auto factor_panel = [&](auto Kf_c, int k0) __attribute__((always_inline)) {
+    constexpr int i0 = 16 * decltype(Kf_c)::value;
     T Ld[4][4], rinv[4], piv[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c)
@@ -353,24 +375,24 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
       for (int r = 0; r < 4; ++r) Ld[r][c] = r >= c ? -pan[c * PS + k0 + r] : T(0);   // panel holds -A
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const bool real = k0 + c < p;
+      // (columns at and beyond p come out as whatever the border row makes of
+      // them; the pass below sets them to identity)
       T dsum = Ld[c][c];
 #pragma unroll
       for (int j = 0; j < c; ++j) dsum -= Ld[c][j] * Ld[c][j];
-      piv[c] = real ? dsum : T(1);
-      const T ri = real ? M::rsqrt(dsum) : T(1);
+      piv[c] = dsum;
+      const T ri = M::rsqrt(dsum);
       rinv[c] = ri;
-      Ld[c][c] = real ? dsum * ri : T(1);
+      Ld[c][c] = dsum * ri;
 #pragma unroll
       for (int r = c + 1; r < 4; ++r) {
         T v = Ld[r][c];
 #pragma unroll
         for (int j = 0; j < c; ++j) v -= Ld[r][j] * Ld[c][j];
-        Ld[r][c] = real ? v * ri : T(0);
+        Ld[r][c] = v * ri;
       }
     }
-    const int i0 = k0 & ~15;
-    constexpr int NCH = (PS + 63) / 64;   // 64-row chunks of the panel
+    constexpr int NCH = (PS - i0 + 63) / 64;   // 64-row chunks of the panel
     // every chunk's entries are read before any is used (the row index is
     // clamped into the panel; the clamped lanes store nothing)
     T pv[NCH][4];
@@ -381,29 +403,38 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
 #pragma unroll
       for (int c = 0; c < 4; ++c) pv[q][c] = pan[c * PS + ic];
     }
+    // every lane runs the substitution, which also yields the rows of the
+    // diagonal block up to their diagonal (the operations that formed Ld); right
+    // of the diagonal there, and above the block, is zero.  Only the first chunk
+    // holds such rows (i0 + 64 > k0 + 3).  An appended row j stands for column
+    // i0 + j.  FP64 takes all chunks in step (independent chains: a dependent
+    // operation waits as long as two issue), FP32 one after the other (fewer
+    // registers; its dependent operations do not wait).
+    constexpr int QB = sizeof(T) == 8 && !TIGHT ? NCH : 1;
 #pragma unroll
-    for (int q = 0; q < NCH; ++q) {
-      const int i = i0 + ln + 64 * q;
-      if (i < PS) {
-        // every lane runs the substitution, which also yields the rows of the
-        // diagonal block up to their diagonal (the operations that formed Ld);
-        // right of the diagonal there, and above the block, is zero.  Only the
-        // first chunk holds such rows (i0 + 64 > k0 + 3).  An appended row j
-        // stands for column i0 + j.
-        T x[4];
+    for (int q0 = 0; q0 < NCH; q0 += QB) {
+      T x[QB][4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          T v = -pv[q][c];
+      for (int c = 0; c < 4; ++c)
 #pragma unroll
-          for (int j = 0; j < c; ++j) v -= x[j] * Ld[c][j];
-          x[c] = v * rinv[c];
-          if (q == 0) x[c] = (i < P ? i : i0 + (i - P)) - k0 < c && i < P ? T(0) : x[c];
+        for (int q = 0; q < QB; ++q) {
+          const int i = i0 + ln + 64 * (q0 + q);
+          T v = -pv[q0 + q][c];
+#pragma unroll
+          for (int j = 0; j < c; ++j) v -= x[q][j] * Ld[c][j];
+          x[q][c] = v * rinv[c];
+          if (q0 + q == 0) x[q][c] = (i < P ? i : i0 + (i - P)) - k0 < c && i < P ? T(0) : x[q][c];
         }
 #pragma unroll
-        for (int c = 0; c < 4; ++c) pan[c * PS + i] = x[c];
-        if (i == p) {
+      for (int q = 0; q < QB; ++q) {
+        const int i = i0 + ln + 64 * (q0 + q);
+        if (i < PS) {
 #pragma unroll
-          for (int c = 0; c < 4; ++c) swk[k0 + c] = x[c];
+          for (int c = 0; c < 4; ++c) pan[c * PS + i] = x[q][c];
+          if (i == p) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) swk[k0 + c] = x[q][c];
+          }
         }
       }
     }
@@ -431,6 +462,122 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
   };
 
   const int kend = MODE == 4 ? mq : p;   // columns to eliminate
+  auto init_einv = [&](auto K_c) __attribute__((always_inline)) {
+    BV_CV(K);
+    // -e_j for the columns the loop below eliminates; columns it skips (at
+    // and beyond kend: the border column and the padding) keep +e_j, the
+    // identity of the inverse there
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      einv[r] = M::row(lg, r) == lr ? (K * 16 + lr < kend ? T(-1) : T(1)) : T(0);
+  };
+  // inv(L_KK) = (L_KK^-T)^T into the diagonal tile, transposed through LDS
+  auto finish_einv = [&](auto K_c) __attribute__((always_inline)) {
+    BV_CV(K);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) pan[lr * 16 + M::row(lg, r)] = einv[r];
+    wave_lds_sync();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[tix(K, K)][r] = pan[M::row(lg, r) * 16 + lr];
+    wave_lds_sync();
+  };
+  // FP64 (ROWPAN): the panel is kept by rows, pan[row * 4 + c], and its rows are
+  // solved where the matrix instructions want them.  Lane (lr, lg) needs column lg
+  // of L for row lr of each row tile: it forms row lg of the inverse of the 4 x 4
+  // block, z, once per panel (10 operations) and v[I] = sum_c A[row][c] z[c], 4
+  // products per row tile.  The substitution by rows costs fewer operations but
+  // needs its results written to LDS and read back in this layout, one more
+  // exchange in each panel's chain of dependent steps.
+  constexpr bool ROWPAN = sizeof(T) == 8 && !LEFT && !TIGHT;
+  auto publish_rows = [&](auto Kc_c, int c0) __attribute__((always_inline)) {
+    constexpr int Kc = decltype(Kc_c)::value;
+    if (lr >= c0 && lr < c0 + 4) {
+      static_for<Kc, G>(BV_CI(I) {
+        BV_CV(I);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) pan[(I * 16 + M::row(lg, r)) * 4 + lr - c0] = acc[tix(I, Kc)][r];
+        __builtin_amdgcn_sched_barrier(0);   // one tile's copies at a time in the VGPRs
+      });
+      if (EINV) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) pan[(P + M::row(lg, r)) * 4 + lr - c0] = einv[r];
+      }
+    }
+  };
+  // lower part of the 4 x 4 block at column k0 of the published panel (-A)
+  auto read_block = [&](int k0, T (&D)[4][4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int c = 0; c <= r; ++c) D[r][c] = pan[(k0 + r) * 4 + c];
+  };
+  // Cholesky of the block (same values in every lane), pivots to LDS; z = -(row
+  // lg of the inverse), the sign for the panel's -A
+  auto factor_block = [&](int k0, T (&D)[4][4], T (&z)[4]) __attribute__((always_inline)) {
+    if (k0 + 4 > p) {   // columns at and beyond p: identity
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c <= r; ++c)
+          if (k0 + r >= p) D[r][c] = r == c ? T(-1) : T(0);
+    }
+    T piv[4], rinv[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int j = 0; j < c; ++j) D[c][c] += D[c][j] * D[c][j];
+      piv[c] = -D[c][c];
+      rinv[c] = M::rsqrt(piv[c]);
+#pragma unroll
+      for (int r = c + 1; r < 4; ++r) {
+#pragma unroll
+        for (int j = 0; j < c; ++j) D[r][c] += D[r][j] * D[c][j];
+        D[r][c] = -D[r][c] * rinv[c];
+      }
+    }
+#pragma unroll
+    for (int c = 3; c >= 0; --c) {
+      T v = lg == c ? T(-1) : T(0);
+#pragma unroll
+      for (int j = c + 1; j < 4; ++j) v -= z[j] * D[j][c];
+      z[c] = v * rinv[c];
+    }
+    if (ln == 0) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) sdk[k0 + c] = piv[c];
+    }
+  };
+  // v[I] (and ve, the appended rows) of the published panel; border entries to LDS
+  auto solve_rows = [&](auto K_c, int k0, const T (&z)[4], T (&v)[G], T& ve) __attribute__((always_inline)) {
+    BV_CV(K);
+    // the next row tile's entries are read before the current one's products
+    // (no more: the scheduler would read all of them first and spill)
+    T cur[4], nxt[4];
+    auto fetch = [&](int row, T (&d)[4]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) d[c] = pan[row * 4 + c];
+    };
+    auto dot = [&]() __attribute__((always_inline)) { return cur[0] * z[0] + cur[1] * z[1] + (cur[2] * z[2] + cur[3] * z[3]); };
+    fetch(16 * K + lr, cur);
+    static_for<K, G + (EINV ? 1 : 0)>(BV_CI(I) {
+      BV_CV(I);
+      if constexpr (I + 1 < G + (EINV ? 1 : 0)) fetch((I + 1) * 16 + lr, nxt);
+      if constexpr (I < G) v[I] = dot();
+      else ve = dot();
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) cur[c] = nxt[c];
+    });
+    // above the block, and right of the diagonal in it, L is zero (columns at and
+    // beyond p have entries in rows from p on only, which nothing reads)
+    if (lr < k0 - 16 * K + lg) v[K] = T(0);
+    // the border row's entries of the four columns
+    T w = T(0);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) w += pan[p * 4 + c] * z[c];
+    if (lr == 0) swk[k0 + lg] = w;
+  };
+
   static_for<0, G>(BV_CI(K) {
     BV_CV(K);
     if (K * 16 >= kend) return;
@@ -461,14 +608,67 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
         });
       }
     }
-    if constexpr (EINV) {
-      // -e_j for the columns the loop below eliminates; columns it skips (at
-      // and beyond kend: the border column and the padding) keep +e_j, the
-      // identity of the inverse there
+    if constexpr (EINV && !ROWPAN) init_einv(K_c);
+    if constexpr (ROWPAN) {
+      // One step per panel: its rows are solved, then tile column K (which holds the
+      // next panel) takes the rank-4 update and the next panel is published and its
+      // block read before the update of the other tiles is issued, which covers
+      // the LDS exchange.
+      constexpr bool KEEP = MODE != 0 && MODE != 4;   // the finished columns stay in the tiles
+      T D[4][4];
+      if constexpr (EINV) init_einv(K_c);
+      publish_rows(K_c, 0);
+      wave_lds_sync();
+      read_block(K * 16, D);
+#pragma nounroll
+      for (int c0 = 0;; c0 += 4) {
+        const int k0 = K * 16 + c0;
+        T z[4], v[G], ve = T(0);
+        factor_block(k0, D, z);
+        solve_rows(K_c, k0, z, v, ve);
+        const bool next = c0 + 4 < 16 && k0 + 4 < kend;
+        if (MODE == 4 ? c0 + 4 < 16 : next) {   // (prediction: the block's columns may start in this tile)
+          static_for<K, G>(BV_CI(I) {
+            BV_CV(I);
+            acc[tix(I, K)] = M::op(v[I], v[K], acc[tix(I, K)]);
+          });
+          if (EINV) einv = M::op(ve, v[K], einv);
+        }
+        if constexpr (KEEP) {
+          wave_lds_sync();
+          static_for<K, G>(BV_CI(I) {
+            BV_CV(I);
+            pan[(I * 16 + lr) * 4 + lg] = v[I];
+          });
+          if (EINV) pan[(P + lr) * 4 + lg] = ve;
+          wave_lds_sync();
+          if (lr >= c0 && lr < c0 + 4) {
+            static_for<K, G>(BV_CI(I) {
+              BV_CV(I);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        einv[r] = M::row(lg, r) == lr ? (K * 16 + lr < kend ? T(-1) : T(1)) : T(0);
-    }
+              for (int r = 0; r < 4; ++r) acc[tix(I, K)][r] = pan[(I * 16 + M::row(lg, r)) * 4 + lr - c0];
+            });
+            if (EINV) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) einv[r] = pan[(P + M::row(lg, r)) * 4 + lr - c0];
+            }
+          }
+        }
+        wave_lds_sync();
+        static_for<K + 1, G>(BV_CI(I) {
+          BV_CV(I);
+          static_for<K + 1, I + 1>(BV_CI(J) {
+            BV_CV(J);
+            acc[tix(I, J)] = M::op(v[I], v[J], acc[tix(I, J)]);
+          });
+        });
+        if (next) publish_rows(K_c, c0 + 4);
+        wave_lds_sync();
+        if (next) read_block(k0 + 4, D);
+        if (!next) break;
+      }
+      if constexpr (EINV) finish_einv(K_c);
+    } else
     if constexpr (sizeof(T) == 4 && (MODE == 5 || MODE == 2)) {
       // FP32 gradient, one step per panel of four columns: the rank-4 update of tile
       // column K first (the next panel's columns are in it) and the finished
@@ -479,7 +679,7 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
       // the value and prediction kernels measured faster in it as well.)
       publish(std::integral_constant<int, K>{}, 0);
       wave_lds_sync();
-      factor_panel(K * 16);
+      factor_panel(K_c, K * 16);
       wave_lds_sync();
 #pragma nounroll
       for (int c0 = 0;; c0 += 4) {
@@ -488,11 +688,15 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
           BV_CV(I);
           v[I] = pan[lg * PS + I * 16 + lr];
         });
-        static_for<K, G>(BV_CI(I) {
-          BV_CV(I);
-          acc[tix(I, K)] = M::op(v[I], v[K], acc[tix(I, K)]);
-        });
-        if (EINV) einv = M::op(pan[lg * PS + P + lr], v[K], einv);
+        // the tile column's last panel leaves no column of it to update
+        const bool next = c0 + 4 < 16 && K * 16 + c0 + 4 < kend;
+        if (next) {
+          static_for<K, G>(BV_CI(I) {
+            BV_CV(I);
+            acc[tix(I, K)] = M::op(v[I], v[K], acc[tix(I, K)]);
+          });
+          if (EINV) einv = M::op(pan[lg * PS + P + lr], v[K], einv);
+        }
         if (MODE != 0 && MODE != 4 && lr >= c0 && lr < c0 + 4) {
           // keep the finished factor columns in the tiles
           static_for<K, G>(BV_CI(I) {
@@ -515,13 +719,12 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
             });
           });
         };
-        const bool next = c0 + 4 < 16 && K * 16 + c0 + 4 < kend;
         wave_lds_sync();
         if (next) publish(std::integral_constant<int, K>{}, c0 + 4);
         wave_lds_sync();
         trailing();
         if (!next) break;
-        factor_panel(K * 16 + c0 + 4);
+        factor_panel(K_c, K * 16 + c0 + 4);
         wave_lds_sync();
       }
     } else {
@@ -531,21 +734,41 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
         if (k0 >= kend) break;
         publish(std::integral_constant<int, K>{}, c0);
         wave_lds_sync();
-        factor_panel(k0);
+        factor_panel(K_c, k0);
         wave_lds_sync();
         T v[G];
         static_for<K, G>(BV_CI(I) {
           BV_CV(I);
           v[I] = pan[lg * PS + I * 16 + lr];
         });
-        static_for<K, G>(BV_CI(I) {
-          BV_CV(I);
-          static_for<K, (LEFT ? K + 1 : I + 1)>(BV_CI(J) {   // mode 6: its own tile column only
-            BV_CV(J);
-            acc[tix(I, J)] = M::op(v[I], v[J], acc[tix(I, J)]);
+        if constexpr (TIGHT) {
+          static_for<K, G>(BV_CI(I) {
+            BV_CV(I);
+            static_for<K, I + 1>(BV_CI(J) {
+              BV_CV(J);
+              acc[tix(I, J)] = M::op(v[I], v[J], acc[tix(I, J)]);
+            });
           });
-        });
-        if (EINV) einv = M::op(pan[lg * PS + P + lr], v[K], einv);
+          if (EINV) einv = M::op(pan[lg * PS + P + lr], v[K], einv);
+        } else {
+          // the tile column itself, unless this was its last panel
+          if (c0 + 4 < 16) {
+            static_for<K, G>(BV_CI(I) {
+              BV_CV(I);
+              acc[tix(I, K)] = M::op(v[I], v[K], acc[tix(I, K)]);
+            });
+            if (EINV) einv = M::op(pan[lg * PS + P + lr], v[K], einv);
+          }
+          if constexpr (!LEFT) {   // the tiles right of it (mode 6 updates those when their turn comes)
+            static_for<K + 1, G>(BV_CI(I) {
+              BV_CV(I);
+              static_for<K + 1, I + 1>(BV_CI(J) {
+                BV_CV(J);
+                acc[tix(I, J)] = M::op(v[I], v[J], acc[tix(I, J)]);
+              });
+            });
+          }
+        }
         if (MODE != 0 && MODE != 4 && lr >= c0 && lr < c0 + 4) {
           // keep the finished factor columns in the tiles
           static_for<K, G>(BV_CI(I) {
@@ -561,15 +784,7 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
         wave_lds_sync();
       }
     }
-    if constexpr (EINV) {
-      // inv(L_KK) = (L_KK^-T)^T into the diagonal tile, transposed through LDS
-#pragma unroll
-      for (int r = 0; r < 4; ++r) pan[lr * 16 + M::row(lg, r)] = einv[r];
-      wave_lds_sync();
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[tix(K, K)][r] = pan[M::row(lg, r) * 16 + lr];
-      wave_lds_sync();
-    }
+    if constexpr (EINV && !ROWPAN) finish_einv(K_c);
     if constexpr (LEFT) {
       // the finished tile column to the item's slot; the later columns read it
       // back through global memory (hence the workgroup barrier)
@@ -689,10 +904,9 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
   const T irange = T(th.inv_range);
   T dh0 = T(0), dh1 = T(0), dh2 = T(0);   // closed forms: d rho / d range coefficients over the range
   if constexpr (!GEN) {
-    const double u1 = LOG2U ? kLn2 : 1.0;
-    dh0 = T((double)mc.g0 * th.inv_range * u1);
-    dh1 = T((double)mc.g1 * th.inv_range * u1 * u1);
-    dh2 = T((double)mc.g2 * th.inv_range * u1 * u1 * u1);
+    dh0 = T((double)mc.g0 * th.inv_range * kLn2);
+    dh1 = T((double)mc.g1 * th.inv_range * kLn2 * kLn2);
+    dh2 = T((double)mc.g2 * th.inv_range * kLn2 * kLn2 * kLn2);
   }
   // d/d sigma2 needs no entry of dK: with d K_J / d sigma2 = (K_J - nugget I) / sigma2,
   // <W, K_J> = ||w||^2 - ||w_N||^2 - l (the quadratic forms of y_J and y_N, and
@@ -734,17 +948,33 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
           if (kq < nk) c = M::op(av[kq], xb[kq], c);
         return c;
       };
-      acc_t cn = wtile(0);
+      // (with two FP64 waves per SIMD the other wave covers it, and there are no
+      // registers for a second tile)
+      constexpr bool AHEAD = !(sizeof(T) == 8 && wave_min_waves<T, G, MODE, GEN>() >= 2);
+      acc_t cn;
+      if constexpr (AHEAD) cn = wtile(0);
       for (int J = 0; J <= I; ++J) {
-        const acc_t c = cn;
-        if (J < I) cn = wtile(J + 1);
+        acc_t c;
+        if constexpr (AHEAD) {
+          c = cn;
+          if (J < I) cn = wtile(J + 1);
+        } else {
+          c = wtile(J);
+        }
         const int j = J * 16 + lr;
         const T sj0 = su[j], sj1 = su[P + j], sj2 = su[2 * P + j];
         T s1 = T(0), s2 = T(0), s3 = T(0);
+        T dx[4], dy[4], dz[4], u[4], e[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          dx[r] = ri[r][0] - sj0;
+          dy[r] = ri[r][1] - sj1;
+          dz[r] = ri[r][2] - sj2;
+        }
+        if constexpr (!GEN) distance_exp2neg4<STAGED>(dx, dy, dz, u, e);
         auto entry = [&](int r) __attribute__((always_inline)) {
-          const T dx = ri[r][0] - sj0, dy = ri[r][1] - sj1, dz = ri[r][2] - sj2;
-          const T x = sqrt_fast<T>(dx * dx + dy * dy + dz * dz);
           if constexpr (GEN) {
+            const T x = distance<T>(dx[r], dy[r], dz[r]);
             if (want_nu) {
               T dr, dn;
               mc.drange_dnu(x, irange, dr, dn);
@@ -754,8 +984,7 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE>())) bv_wave_ke
               s1 += c[r] * mc.drange(x, irange);
             }
           } else {
-            if constexpr (LOG2U) s1 += c[r] * mc.drange_scaled_log2(x, dh0, dh1, dh2);
-            else s1 += c[r] * mc.drange_scaled(x, dh0, dh1, dh2);
+            s1 += c[r] * mc.drange_log2(u[r], e[r], dh0, dh1, dh2);
           }
         };
         if ((I + 1) * 16 <= p) {   // a tile inside the point rows (wave-uniform)
@@ -1083,7 +1312,16 @@ static hipError_t launch_wave_t(int g, const AdjArgs& a, const ThetaPack& thp, i
       if (g == 11) return launch_wave_g<T, 11, MODE, GEN>(a, thp, grid, s);
     }
     return hipErrorInvalidValue;
-  } else if constexpr (MODE == 1 && sizeof(T) == 4) {   // FP32 G >= 10 use the split gradient
+  } else if constexpr (MODE == 1 && sizeof(T) == 8) {
+    // the classes that neither keep the factor in registers nor split: G = 9 with
+    // several passes of right-hand sides, and the Bessel form above it
+    if (g == 9) return launch_wave_g<T, 9, MODE, GEN>(a, thp, grid, s);
+    if constexpr (GEN) {
+      if (g == 10) return launch_wave_g<T, 10, MODE, GEN>(a, thp, grid, s);
+      if (g == 11) return launch_wave_g<T, 11, MODE, GEN>(a, thp, grid, s);
+    }
+    return hipErrorInvalidValue;
+  } else if constexpr (MODE == 1) {   // FP32 G >= 10 use the split gradient
     switch (g) {
       case 1: return launch_wave_g<T, 1, MODE, GEN>(a, thp, grid, s);
       case 2: return launch_wave_g<T, 2, MODE, GEN>(a, thp, grid, s);
