@@ -2,10 +2,11 @@
 // block permutation zeta, and the m nearest earlier neighbours of each block
 // centroid (Alg. 1, nearest neighbours).  Untimed in the paper's convention.
 //
-// K-means: Lloyd iterations in FP64.  Assignment is exhaustive over the
-// centroids (staged through LDS, ascending index, strict '<' so ties go to
-// the lower index).  Centroid sums use 64-bit fixed point (exact integer
-// atomics), so every run produces the same centroids bit for bit.
+// K-means: Lloyd iterations in FP64.  Assignment walks a grid of cells that
+// lists the centroids (below 128 blocks it is exhaustive over the centroids,
+// staged through LDS); both are exact, ties go to the lower index.  Centroid sums
+// use 64-bit fixed point (exact integer atomics), so every run produces the same
+// centroids bit for bit.
 //
 // Neighbours: exact search on a uniform grid of cells over the metric-scaled
 // points.  Points are sorted by cell with ascending index inside a cell, so
@@ -78,6 +79,11 @@ __global__ void __launch_bounds__(256) bbox_kernel(const double* __restrict__ lo
 
 // ---------------------------------------------------------------- kmeans --
 
+// Iterations: one kernel turns the sums into centroids and hangs each into the
+// list of its grid cell, one assigns the points and adds them to the new sums.
+// Both read the flags of the iteration before, so the host launches
+// several iterations ahead and looks at the flags once for all of them.
+
 struct KmArgs {
   const double* locs;
   int64_t n;
@@ -87,29 +93,148 @@ struct KmArgs {
   double fscale;     // fixed-point units per coordinate unit
   int bc;
   double* cent;      // bc x 3 (unused dims 0)
-  int* label;        // n
-  int* changed;      // 1 int
+  int* label;        // n, original point order
   unsigned long long* fsum;  // bc x 3 fixed-point sums
-  int* cnt;          // bc
+  int* cnt;          // 2 x bc: point counts, the two sets in turn (set t & 1 before update t)
   double* dist;      // n: squared distance to own centroid (for re-seeding)
+  const double* xs;  // grid path: the points in cell order (n x d, not scaled), and
+  int* lab;          //   their labels in that order; else locs and label
+};
+
+// A uniform grid of cubic cells (side h, in the scaled coordinates, over the
+// points' bounding box) holds the centroids, about two per cell, as one linked
+// list per cell; each point searches rings of cells around its own until the
+// next ring is farther than the best distance found.  A centroid in a cell r+1
+// rings away is at least r h from the point, so the search is exact; ties go
+// to the lowest centroid index, as in the exhaustive kernel.  The points are put
+// in cell order once, so that the lanes of a wave walk the same cells.
+// n = 2e5, 20,000 blocks in 2-D: one assignment 2.04 ms exhaustive (2e12
+// distances/s).
+constexpr int64_t kKmGridMinBlocks = 128;   // below, the exhaustive kernel's few rounds cost less than the cell walk
+// and above, the walk is taken while the lists it visits hold fewer than a
+// quarter of the centroids: a step of a list waits for memory, a step of the
+// exhaustive kernel reads LDS
+constexpr int64_t kKmWalkRatio = 4;
+
+struct KmGrid {
+  double lo[3];
+  double h, inv_h;
+  int nc[3];
+  int ncell;
+  int* head[2];   // ncell + 1: first centroid of each cell or -1, two sets in turn
+  int* next;      // bc
+};
+
+// flags of iteration t of a run of launches (null: none to look at)
+struct KmFlags {
+  const int* prev_changed;   // 0: the iteration before changed no label (or did not run)
+  int* nempty;               // clusters without points
+  int* changed;              // 1: some label changed (null: the first assignment)
 };
 
 __global__ void km_init_kernel(KmArgs a, const int64_t* __restrict__ init_idx) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= a.bc) return;
   const int64_t p = init_idx[c];
-  for (int k = 0; k < 3; ++k) a.cent[c * 3 + k] = k < a.d ? a.locs[p * a.d + k] * a.w[k] : 0.0;
+  a.cnt[c] = a.cnt[a.bc + c] = 0;
+  for (int k = 0; k < 3; ++k) {
+    a.cent[c * 3 + k] = k < a.d ? a.locs[p * a.d + k] * a.w[k] : 0.0;
+    a.fsum[c * 3 + k] = 0ull;
+  }
+}
+
+__device__ inline int km_grid_cell(const KmGrid& g, const double* x, int d, int* pc) {
+  int cell = 0, stride = 1;
+  for (int k = 0; k < 3; ++k) {
+    int c = 0;
+    if (k < d) {
+      const double t = floor((x[k] - g.lo[k]) * g.inv_h);
+      c = !(t >= 0.0) ? 0 : (t >= (double)g.nc[k] ? g.nc[k] - 1 : (int)t);
+    }
+    pc[k] = c;
+    cell += c * stride;
+    stride *= g.nc[k];
+  }
+  return cell;
+}
+
+// cell of each point, and the points in cell order (order: the sorted indices)
+__global__ void km_cell_key_kernel(KmArgs a, KmGrid g, int* __restrict__ key, int64_t* __restrict__ val) {
+#pragma clang fp contract(off)
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= a.n) return;
+  double x[3] = {0, 0, 0};
+  for (int k = 0; k < a.d; ++k) x[k] = a.locs[i * a.d + k] * a.w[k];
+  int pc[3];
+  key[i] = km_grid_cell(g, x, a.d, pc);
+  val[i] = i;
+}
+
+__global__ void km_gather_kernel(KmArgs a, const int64_t* __restrict__ order, double* __restrict__ xs) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= a.n) return;
+  const int64_t o = order[i];
+  for (int k = 0; k < a.d; ++k) xs[i * a.d + k] = a.locs[o * a.d + k];
+}
+
+__global__ void km_labels_out_kernel(KmArgs a, const int64_t* __restrict__ order) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < a.n) a.label[order[i]] = a.lab[i];
+}
+
+__device__ inline void km_insert(const KmArgs& a, const KmGrid& g, int set, int c) {
+  int pc[3];
+  const double x[3] = {a.cent[(size_t)c * 3], a.cent[(size_t)c * 3 + 1], a.cent[(size_t)c * 3 + 2]};
+  g.next[c] = atomicExch(&g.head[set][km_grid_cell(g, x, a.d, pc)], c);
+}
+
+__global__ void km_insert_kernel(KmArgs a, KmGrid g, int set) {
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c < a.bc) km_insert(a, g, set, c);
+}
+
+// Length of the own cell's list summed over the points, each at most kKmWalkCap:
+// what the cell walk will cost (uneven data can put most centroids in few cells).
+constexpr int kKmWalkCap = 1024;
+__global__ void __launch_bounds__(256) km_walk_kernel(KmArgs a, KmGrid g, int set, unsigned long long* __restrict__ sum) {
+#pragma clang fp contract(off)
+  __shared__ int part;
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (threadIdx.x == 0) part = 0;
+  __syncthreads();
+  if (i < a.n) {
+    double x[3] = {0, 0, 0};
+    for (int k = 0; k < a.d; ++k) x[k] = a.xs[i * a.d + k] * a.w[k];
+    int pc[3], len = 0;
+    for (int c = g.head[set][km_grid_cell(g, x, a.d, pc)]; c >= 0 && len < kKmWalkCap; c = g.next[c]) ++len;
+    atomicAdd(&part, len);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && part) atomicAdd(sum, (unsigned long long)part);
+}
+
+// Adds a point (not scaled) to the fixed-point sums of cluster c.
+__device__ inline void km_add(const KmArgs& a, int set, int c, const double* raw) {
+  atomicAdd(&a.cnt[(size_t)set * a.bc + c], 1);
+  for (int k = 0; k < a.d; ++k) {
+    const double v = __builtin_fma(raw[k], a.w[k], -a.lo[k]) * a.fscale;
+    atomicAdd(&a.fsum[c * 3 + k], (unsigned long long)llrint(v));
+  }
 }
 
 // nearest centroid of each point; centroids staged through LDS in chunks
 constexpr int KM_CHUNK = 512;
-__global__ void __launch_bounds__(256) km_assign_kernel(KmArgs a, int first) {
+__global__ void __launch_bounds__(256) km_assign_kernel(KmArgs a, int set, KmFlags f) {
 #pragma clang fp contract(off)
+  if ((f.prev_changed && !*f.prev_changed) || (f.nempty && *f.nempty)) return;
   __shared__ double sc[KM_CHUNK * 3];
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  double x[3] = {0, 0, 0};
+  double raw[3] = {0, 0, 0}, x[3] = {0, 0, 0};
   if (i < a.n)
-    for (int k = 0; k < a.d; ++k) x[k] = a.locs[i * a.d + k] * a.w[k];
+    for (int k = 0; k < a.d; ++k) {
+      raw[k] = a.locs[i * a.d + k];
+      x[k] = raw[k] * a.w[k];
+    }
   double best = INFINITY;
   int bi = 0;
   for (int c0 = 0; c0 < a.bc; c0 += KM_CHUNK) {
@@ -127,71 +252,23 @@ __global__ void __launch_bounds__(256) km_assign_kernel(KmArgs a, int first) {
     }
   }
   if (i < a.n) {
-    if (!first && a.label[i] != bi) atomicOr(a.changed, 1);
+    if (f.changed && a.label[i] != bi) *f.changed = 1;
     a.label[i] = bi;
-    a.dist[i] = best;
+    km_add(a, set ^ 1, bi, raw);
   }
 }
 
-// Large block counts: a uniform grid of cubic cells (side h, in the scaled
-// coordinates, over the points' bounding box) holds the centroids, about two
-// per cell, and each point searches rings of cells around its own until the
-// next ring is farther than the best distance found.  A centroid in a cell r+1
-// rings away is at least r h from the point, so the search is exact; ties go
-// to the lowest centroid index, as in the exhaustive kernel.
-constexpr int64_t kKmGridMinBlocks = 65536;
-
-struct KmGrid {
-  double lo[3];
-  double h, inv_h;
-  int nc[3];
-  int ncell;
-  int* cstart;   // ncell + 1 (exclusive scan of the counts)
-  int* ccur;     // ncell + 1: counts, then insertion cursors
-  int* cidx;     // bc centroid indices grouped by cell
-};
-
-__device__ inline int km_grid_cell(const KmGrid& g, const double* x, int d, int* pc) {
-  int cell = 0, stride = 1;
-  for (int k = 0; k < 3; ++k) {
-    int c = 0;
-    if (k < d) {
-      const double t = floor((x[k] - g.lo[k]) * g.inv_h);
-      c = !(t >= 0.0) ? 0 : (t >= (double)g.nc[k] ? g.nc[k] - 1 : (int)t);
-    }
-    pc[k] = c;
-    cell += c * stride;
-    stride *= g.nc[k];
-  }
-  return cell;
-}
-
-__global__ void km_grid_count_kernel(KmArgs a, KmGrid g) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= a.bc) return;
-  int pc[3];
-  atomicAdd(&g.ccur[km_grid_cell(g, a.cent + (size_t)c * 3, a.d, pc)], 1);
-}
-
-__global__ void km_grid_cursor_kernel(KmGrid g) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i <= g.ncell) g.ccur[i] = g.cstart[i];
-}
-
-__global__ void km_grid_place_kernel(KmArgs a, KmGrid g) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= a.bc) return;
-  int pc[3];
-  const int pos = atomicAdd(&g.ccur[km_grid_cell(g, a.cent + (size_t)c * 3, a.d, pc)], 1);
-  g.cidx[pos] = c;
-}
-
-__global__ void __launch_bounds__(256) km_assign_grid_kernel(KmArgs a, KmGrid g, int first) {
+__global__ void __launch_bounds__(256) km_assign_grid_kernel(KmArgs a, KmGrid g, int set, KmFlags f) {
 #pragma clang fp contract(off)
+  if ((f.prev_changed && !*f.prev_changed) || (f.nempty && *f.nempty)) return;
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= a.n) return;
-  double x[3] = {0, 0, 0};
-  for (int k = 0; k < a.d; ++k) x[k] = a.locs[i * a.d + k] * a.w[k];
+  const int* head = g.head[set];
+  double raw[3] = {0, 0, 0}, x[3] = {0, 0, 0};
+  for (int k = 0; k < a.d; ++k) {
+    raw[k] = a.xs[i * a.d + k];
+    x[k] = raw[k] * a.w[k];
+  }
   int pc[3];
   km_grid_cell(g, x, a.d, pc);
   const int rmax = max(g.nc[0], max(g.nc[1], g.nc[2]));
@@ -205,14 +282,12 @@ __global__ void __launch_bounds__(256) km_assign_grid_kernel(KmArgs a, KmGrid g,
       for (int o1 = -r1; o1 <= r1; ++o1) {
         const int c1 = pc[1] + o1;
         if (c1 < 0 || c1 >= g.nc[1]) continue;
-        for (int o0 = -r; o0 <= r; ++o0) {
+        // this ring only: every cell of a row on its faces, else the row's two ends
+        const int step = max(abs(o1), abs(o2)) == r || r == 0 ? 1 : 2 * r;
+        for (int o0 = -r; o0 <= r; o0 += step) {
           const int c0 = pc[0] + o0;
           if (c0 < 0 || c0 >= g.nc[0]) continue;
-          if (max(abs(o0), max(abs(o1), abs(o2))) != r) continue;   // this ring only
-          const int cell = c0 + g.nc[0] * (c1 + g.nc[1] * c2);
-          const int q1 = g.cstart[cell + 1];
-          for (int q = g.cstart[cell]; q < q1; ++q) {
-            const int c = g.cidx[q];
+          for (int c = head[c0 + g.nc[0] * (c1 + g.nc[1] * c2)]; c >= 0; c = g.next[c]) {
             const double t0 = x[0] - a.cent[c * 3], t1 = x[1] - a.cent[c * 3 + 1], t2 = x[2] - a.cent[c * 3 + 2];
             const double dd = t0 * t0 + t1 * t1 + t2 * t2;
             if (dd < best || (dd == best && c < bi)) {
@@ -226,40 +301,32 @@ __global__ void __launch_bounds__(256) km_assign_grid_kernel(KmArgs a, KmGrid g,
     const double reach = (double)r * g.h;
     if (reach * reach * (1.0 - 1e-9) > best) break;
   }
-  if (!first && a.label[i] != bi) atomicOr(a.changed, 1);
-  a.label[i] = bi;
-  a.dist[i] = best;
+  if (bi == 0x7fffffff) bi = 0;   // no distance compares (a NaN coordinate), as in the exhaustive kernel
+  if (f.changed && a.lab[i] != bi) *f.changed = 1;
+  a.lab[i] = bi;
+  km_add(a, set ^ 1, bi, raw);
 }
 
-__global__ void km_zero_kernel(KmArgs a) {
+// Iteration t (set = t & 1): centroid = fixed-point mean, the sums and the next
+// counts cleared for the assignment; empty clusters keep their centroid (re-seeded
+// on the host side, which also lists the centroids again).  Grid path: into list
+// set `set`; the other set is cleared.
+__global__ void km_update_kernel(KmArgs a, KmGrid g, int set, KmFlags f) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (f.prev_changed && !*f.prev_changed) return;
+  if (a.xs && c <= g.ncell) g.head[set ^ 1][c] = -1;
   if (c >= a.bc) return;
-  a.cnt[c] = 0;
-  for (int k = 0; k < 3; ++k) a.fsum[c * 3 + k] = 0ull;
-}
-
-__global__ void km_accum_kernel(KmArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.n) return;
-  const int c = a.label[i];
-  atomicAdd(&a.cnt[c], 1);
-  for (int k = 0; k < a.d; ++k) {
-    const double v = (a.locs[i * a.d + k] * a.w[k] - a.lo[k]) * a.fscale;
-    atomicAdd(&a.fsum[c * 3 + k], (unsigned long long)llrint(v));
-  }
-}
-
-// centroid = fixed-point mean; empty clusters keep their centroid (re-seeded on the host side)
-__global__ void km_update_kernel(KmArgs a, int* __restrict__ nempty) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= a.bc) return;
-  const int m = a.cnt[c];
+  const int m = a.cnt[(size_t)set * a.bc + c];
+  a.cnt[(size_t)(set ^ 1) * a.bc + c] = 0;
   if (m == 0) {
-    atomicAdd(nempty, 1);
-    return;
+    atomicAdd(f.nempty, 1);
+  } else {
+    for (int k = 0; k < a.d; ++k) {
+      a.cent[c * 3 + k] = a.lo[k] + ((double)a.fsum[c * 3 + k] / a.fscale) / (double)m;
+      a.fsum[c * 3 + k] = 0ull;
+    }
   }
-  for (int k = 0; k < a.d; ++k)
-    a.cent[c * 3 + k] = a.lo[k] + ((double)a.fsum[c * 3 + k] / a.fscale) / (double)m;
+  if (a.xs) km_insert(a, g, set, c);
 }
 
 // squared distance of each point to its (updated) centroid, for re-seeding
@@ -633,9 +700,11 @@ size_t sort_temp_bytes_i32_i32(int64_t n, int nbits = 32) {
   return sz;
 }
 
+constexpr int kKmAhead = 8;   // K-means iterations launched before their flags are read
+
 struct BlocksLayout {
   size_t cent, label, fsum, cnt, dist, changed, key, val, key2, val2, pol, kcnt, part, parti, sort, total;
-  size_t gstart, gcur, gidx, gscan;   // centroid grid (large block counts only)
+  size_t ghead, gnext, gxs, glab;     // centroid grid (all but the smallest block counts)
   int64_t gcells;                     // cell capacity of the grid
 };
 BlocksLayout blocks_layout(int64_t n, int64_t bc) {
@@ -644,9 +713,9 @@ BlocksLayout blocks_layout(int64_t n, int64_t bc) {
   L.cent = o;    o = al256(o + sizeof(double) * 3 * bc);
   L.label = o;   o = al256(o + sizeof(int) * n);
   L.fsum = o;    o = al256(o + sizeof(unsigned long long) * 3 * bc);
-  L.cnt = o;     o = al256(o + sizeof(int) * bc);
+  L.cnt = o;     o = al256(o + sizeof(int) * 2 * bc);
   L.dist = o;    o = al256(o + sizeof(double) * n);
-  L.changed = o; o = al256(o + sizeof(int) * 8);
+  L.changed = o; o = al256(o + sizeof(int) * 64);
   L.key = o;     o = al256(o + sizeof(int) * n);
   L.val = o;     o = al256(o + sizeof(int64_t) * n);
   L.key2 = o;    o = al256(o + sizeof(int) * n);
@@ -657,16 +726,13 @@ BlocksLayout blocks_layout(int64_t n, int64_t bc) {
   L.parti = o;   o = al256(o + sizeof(int64_t) * 1024);
   L.sort = o;    o = al256(o + sort_temp_bytes_i32_i64(n));
   L.gcells = 0;
-  L.gstart = L.gcur = L.gidx = L.gscan = o;
+  L.ghead = L.gnext = L.gxs = L.glab = o;
   if (bc >= kKmGridMinBlocks) {
     L.gcells = 2 * bc + 64;
-    L.gstart = o; o = al256(o + sizeof(int) * (L.gcells + 1));
-    L.gcur = o;   o = al256(o + sizeof(int) * (L.gcells + 1));
-    L.gidx = o;   o = al256(o + sizeof(int) * bc);
-    size_t sc = 0;
-    (void)exclusive_sum((void*)nullptr, sc, (const int*)nullptr, (int*)nullptr, (int)(L.gcells + 1),
-                                     (hipStream_t)0);
-    L.gscan = o;  o = al256(o + sc);
+    L.ghead = o; o = al256(o + sizeof(int) * 2 * (L.gcells + 1));
+    L.gnext = o; o = al256(o + sizeof(int) * bc);
+    L.gxs = o;   o = al256(o + sizeof(double) * 3 * n);
+    L.glab = o;  o = al256(o + sizeof(int) * n);
   }
   L.total = o;
   return L;
@@ -705,31 +771,27 @@ void km_grid_setup(const BlocksLayout& L, void* ws, int64_t bc, int d, const dou
   }
   g.h = h;
   g.inv_h = 1.0 / h;
-  g.cstart = at<int>(ws, L.gstart);
-  g.ccur = at<int>(ws, L.gcur);
-  g.cidx = at<int>(ws, L.gidx);
+  g.head[0] = at<int>(ws, L.ghead);
+  g.head[1] = g.head[0] + L.gcells + 1;
+  g.next = at<int>(ws, L.gnext);
 }
 
-// nearest centroid of every point: exhaustive for small block counts, through
-// the centroid grid (rebuilt from the current centroids) for large ones
-int km_assign(const KmArgs& a, const BlocksLayout& L, void* ws, const KmGrid* g, int first, hipStream_t s) {
+// nearest centroid of every point: exhaustive for the smallest block counts,
+// through the centroid lists `set` of the grid for the others
+hipError_t km_assign(const KmArgs& a, const KmGrid& g, int set, const KmFlags& f, hipStream_t s) {
   const int gn = cdiv64(a.n, 256);
-  if (!g) {
-    hipLaunchKernelGGL(km_assign_kernel, dim3(gn), dim3(256), 0, s, a, first);
-    PCHECK(hipGetLastError());
-    return VECCHIA_OK;
-  }
-  const int gb = cdiv64(a.bc, 256);
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(cdiv64(g->ncell + 1, 256)), dim3(256), 0, s, g->ccur, g->ncell + 1, 0);
-  hipLaunchKernelGGL(km_grid_count_kernel, dim3(gb), dim3(256), 0, s, a, *g);
-  PCHECK(hipGetLastError());
-  size_t tmp = L.total - L.gscan;
-  PCHECK(exclusive_sum(at<void>(ws, L.gscan), tmp, g->ccur, g->cstart, g->ncell + 1, s));
-  hipLaunchKernelGGL(km_grid_cursor_kernel, dim3(cdiv64(g->ncell + 1, 256)), dim3(256), 0, s, *g);
-  hipLaunchKernelGGL(km_grid_place_kernel, dim3(gb), dim3(256), 0, s, a, *g);
-  hipLaunchKernelGGL(km_assign_grid_kernel, dim3(gn), dim3(256), 0, s, a, *g, first);
-  PCHECK(hipGetLastError());
-  return VECCHIA_OK;
+  if (a.xs)
+    hipLaunchKernelGGL(km_assign_grid_kernel, dim3(gn), dim3(256), 0, s, a, g, set, f);
+  else
+    hipLaunchKernelGGL(km_assign_kernel, dim3(gn), dim3(256), 0, s, a, set, f);
+  return hipGetLastError();
+}
+
+// the centroids into the (emptied) lists `set`
+hipError_t km_list(const KmArgs& a, const KmGrid& g, int set, hipStream_t s) {
+  hipLaunchKernelGGL(fill_i32_kernel, dim3(cdiv64(g.ncell + 1, 256)), dim3(256), 0, s, g.head[set], g.ncell + 1, -1);
+  hipLaunchKernelGGL(km_insert_kernel, dim3(cdiv64(a.bc, 256)), dim3(256), 0, s, a, g, set);
+  return hipGetLastError();
 }
 
 int bbox(const double* locs, int64_t n, int d, const double* w, double* part, double* lo, double* hi, hipStream_t s) {
@@ -802,77 +864,116 @@ extern "C" int vecchia_blocks(const double* locs, int64_t n, int32_t d, const do
   a.bc = (int)bc;
   a.cent = at<double>(workspace, L.cent);
   a.label = at<int>(workspace, L.label);
-  a.changed = at<int>(workspace, L.changed);
+  int* const a_changed = at<int>(workspace, L.changed);
   a.fsum = at<unsigned long long>(workspace, L.fsum);
   a.cnt = at<int>(workspace, L.cnt);
   a.dist = at<double>(workspace, L.dist);
   const int gb = cdiv64(bc, 256), gn = cdiv64(n, 256);
   KmGrid grid;
-  const KmGrid* gp = nullptr;
-  if (L.gcells > 0) {
+  memset(&grid, 0, sizeof(grid));
+  int64_t* order = at<int64_t>(workspace, L.val2);   // the points in cell order (grid path)
+  bool finite = true;   // (an infinite extent has no cells)
+  for (int k = 0; k < d; ++k) finite = finite && std::isfinite(hi[k] - lo[k]);
+  if (L.gcells > 0 && finite) {
     km_grid_setup(L, workspace, bc, d, lo, hi, grid);
-    gp = &grid;
+    int* key = at<int>(workspace, L.key);
+    int64_t* val = at<int64_t>(workspace, L.val);
+    hipLaunchKernelGGL(km_cell_key_kernel, dim3(gn), dim3(256), 0, s, a, grid, key, val);
+    PCHECK(hipGetLastError());
+    int nbits = 1;
+    while (((int64_t)1 << nbits) < grid.ncell) ++nbits;
+    size_t tmp = sort_temp_bytes_i32_i64(n, nbits);
+    if (L.sort + tmp > ws_bytes) return VECCHIA_ENOMEM;
+    PCHECK(radix_sort(at<void>(workspace, L.sort), tmp, key, at<int>(workspace, L.key2), val, order, (int)n, 0, nbits,
+                      s));
+    double* xs = at<double>(workspace, L.gxs);
+    hipLaunchKernelGGL(km_gather_kernel, dim3(gn), dim3(256), 0, s, a, order, xs);
+    a.xs = xs;
+    a.lab = at<int>(workspace, L.glab);
   }
   hipLaunchKernelGGL(km_init_kernel, dim3(gb), dim3(256), 0, s, a, init_idx);
   PCHECK(hipGetLastError());
-  st = km_assign(a, L, workspace, gp, 1, s);
-  if (st) return st;
-  int it = 0;
-  for (; it < max_iter; ++it) {
-    hipLaunchKernelGGL(km_zero_kernel, dim3(gb), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, a.changed, 8, 0);
-    hipLaunchKernelGGL(km_accum_kernel, dim3(gn), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(km_update_kernel, dim3(gb), dim3(256), 0, s, a, a.changed + 1);
+  if (a.xs) {
+    PCHECK(km_list(a, grid, 1, s));
+    hipLaunchKernelGGL(fill_i32_kernel, dim3(cdiv64(grid.ncell + 1, 256)), dim3(256), 0, s, grid.head[0],
+                       grid.ncell + 1, -1);
+    unsigned long long* walk = reinterpret_cast<unsigned long long*>(a_changed + 32);
+    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, a_changed, 34, 0);
+    hipLaunchKernelGGL(km_walk_kernel, dim3(gn), dim3(256), 0, s, a, grid, 1, walk);
     PCHECK(hipGetLastError());
-    int hflags[2];
-    PCHECK(hipMemcpyAsync(hflags, a.changed, sizeof(hflags), hipMemcpyDeviceToHost, s));
+    unsigned long long hw = 0;
+    PCHECK(hipMemcpyAsync(&hw, walk, sizeof(hw), hipMemcpyDeviceToHost, s));
     PCHECK(hipStreamSynchronize(s));
-    const int nempty = hflags[1];
-    if (nempty > 0) {
-      // re-seed each empty cluster, in cluster order, with the point farthest
-      // from its updated centroid (each point at most once)
-      hipLaunchKernelGGL(km_dist_kernel, dim3(gn), dim3(256), 0, s, a);
-      PCHECK(hipGetLastError());
-      std::vector<int> hc(bc);
-      PCHECK(hipMemcpyAsync(hc.data(), a.cnt, sizeof(int) * bc, hipMemcpyDeviceToHost, s));
-      PCHECK(hipStreamSynchronize(s));
-      const int grid = std::min(1024, gn);
-      for (int64_t c = 0; c < bc; ++c) {
-        if (hc[c] != 0) continue;
-        hipLaunchKernelGGL(argmax_kernel, dim3(grid), dim3(256), 0, s, a.dist, n, at<double>(workspace, L.part),
-                           at<int64_t>(workspace, L.parti));
-        std::vector<double> pv(grid);
-        std::vector<int64_t> pi(grid);
-        PCHECK(hipMemcpyAsync(pv.data(), at<double>(workspace, L.part), sizeof(double) * grid, hipMemcpyDeviceToHost, s));
-        PCHECK(hipMemcpyAsync(pi.data(), at<int64_t>(workspace, L.parti), sizeof(int64_t) * grid,
-                              hipMemcpyDeviceToHost, s));
-        PCHECK(hipStreamSynchronize(s));
-        double bv = -INFINITY;
-        int64_t bi = 0;
-        for (int g = 0; g < grid; ++g)
-          if (pv[g] > bv || (pv[g] == bv && pi[g] < bi)) {
-            bv = pv[g];
-            bi = pi[g];
-          }
-        if (bi < 0 || bi >= n) return VECCHIA_EUNSUPPORTED;  // no point left to re-seed with
-        hipLaunchKernelGGL(reseed_kernel, dim3(1), dim3(64), 0, s, a, (int)c, bi);
-      }
+    const double cells = d == 1 ? 3.0 : d == 2 ? 9.0 : 27.0;
+    if (kKmWalkRatio * cells * (double)hw > (double)n * (double)bc) a.xs = nullptr;
+  }
+  const KmFlags none = {nullptr, nullptr, nullptr};
+  PCHECK(km_assign(a, grid, 1, none, s));   // the counts of set 0 are those before update 0
+  const int gu = cdiv64(std::max<int64_t>(bc, a.xs ? grid.ncell + 1 : 0), 256);
+  int* changed = a_changed;                 // [kKmAhead] changed, then [kKmAhead] empty clusters
+  int* nempty = a_changed + kKmAhead;
+  int it = 0;
+  bool done = false;
+  while (!done && it < max_iter) {
+    const int ahead = std::min(kKmAhead, max_iter - it);
+    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, a_changed, 2 * kKmAhead, 0);
+    for (int q = 0; q < ahead; ++q) {
+      const int set = (it + q) & 1;
+      const KmFlags f = {q > 0 ? changed + q - 1 : nullptr, nempty + q, changed + q};
+      hipLaunchKernelGGL(km_update_kernel, dim3(gu), dim3(256), 0, s, a, grid, set, f);
+      PCHECK(km_assign(a, grid, set, f, s));
     }
-    hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, a.changed, 1, 0);
-    st = km_assign(a, L, workspace, gp, 0, s);
-    if (st) return st;
-    int hch = 0;
-    PCHECK(hipMemcpyAsync(&hch, a.changed, sizeof(int), hipMemcpyDeviceToHost, s));
+    int hf[2 * kKmAhead];
+    PCHECK(hipMemcpyAsync(hf, a_changed, sizeof(hf), hipMemcpyDeviceToHost, s));
     PCHECK(hipStreamSynchronize(s));
-    if (!hch && nempty == 0) {
-      ++it;
-      break;
+    for (int q = 0; q < ahead && !done; ++q, ++it) {
+      const int set = it & 1;
+      if (hf[kKmAhead + q] > 0) {
+        // re-seed each empty cluster, in cluster order, with the point farthest
+        // from its updated centroid (each point at most once); the launches after
+        // this update did nothing, so its assignment follows here
+        if (a.xs) hipLaunchKernelGGL(km_labels_out_kernel, dim3(gn), dim3(256), 0, s, a, order);
+        hipLaunchKernelGGL(km_dist_kernel, dim3(gn), dim3(256), 0, s, a);
+        PCHECK(hipGetLastError());
+        std::vector<int> hc(bc);
+        PCHECK(hipMemcpyAsync(hc.data(), a.cnt + (size_t)set * bc, sizeof(int) * bc, hipMemcpyDeviceToHost, s));
+        PCHECK(hipStreamSynchronize(s));
+        const int grid_am = std::min(1024, gn);
+        for (int64_t c = 0; c < bc; ++c) {
+          if (hc[c] != 0) continue;
+          hipLaunchKernelGGL(argmax_kernel, dim3(grid_am), dim3(256), 0, s, a.dist, n, at<double>(workspace, L.part),
+                             at<int64_t>(workspace, L.parti));
+          std::vector<double> pv(grid_am);
+          std::vector<int64_t> pi(grid_am);
+          PCHECK(hipMemcpyAsync(pv.data(), at<double>(workspace, L.part), sizeof(double) * grid_am,
+                                hipMemcpyDeviceToHost, s));
+          PCHECK(hipMemcpyAsync(pi.data(), at<int64_t>(workspace, L.parti), sizeof(int64_t) * grid_am,
+                                hipMemcpyDeviceToHost, s));
+          PCHECK(hipStreamSynchronize(s));
+          double bv = -INFINITY;
+          int64_t bi = 0;
+          for (int g = 0; g < grid_am; ++g)
+            if (pv[g] > bv || (pv[g] == bv && pi[g] < bi)) {
+              bv = pv[g];
+              bi = pi[g];
+            }
+          if (bi < 0 || bi >= n) return VECCHIA_EUNSUPPORTED;  // no point left to re-seed with
+          hipLaunchKernelGGL(reseed_kernel, dim3(1), dim3(64), 0, s, a, (int)c, bi);
+        }
+        if (a.xs) PCHECK(km_list(a, grid, set, s));
+        PCHECK(km_assign(a, grid, set, none, s));
+        ++it;
+        break;
+      }
+      done = hf[q] == 0;
     }
   }
+  if (a.xs) hipLaunchKernelGGL(km_labels_out_kernel, dim3(gn), dim3(256), 0, s, a, order);
+  PCHECK(hipGetLastError());
   if (iters_out) *iters_out = it;
   // order: stable radix sort of points by block position (ascending index inside a block)
   int* pol = at<int>(workspace, L.pol);
-  int* bad = a.changed + 2;
+  int* bad = a_changed;
   hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, s, bad, 1, 0);
   hipLaunchKernelGGL(fill_i32_kernel, dim3(gb), dim3(256), 0, s, pol, (int)bc, -1);
   hipLaunchKernelGGL(pos_of_label_kernel, dim3(gb), dim3(256), 0, s, block_perm, (int)bc, pol, bad);

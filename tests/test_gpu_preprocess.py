@@ -164,3 +164,64 @@ def test_blocks_grid_assignment_large_block_count(n, d, bc):
     inert = ((x - cen[lab]) ** 2).sum()
     print(f"n={n} d={d} bc={bc}: iters {iters}, inertia {inert0:.4e} -> {inert:.4e}")
     assert inert < inert0
+
+
+def _lloyd_fixed_point(s, w, init, max_iter):
+    """Lloyd with centroid sums in 64-bit fixed point, as the library defines
+    them (so that near ties fall the same way): labels after max_iter iterations."""
+    n, x = s.shape[0], s * w
+    lo = x.min(0)
+    ext = (x.max(0) - lo).max()
+    fscale = np.ldexp(1.0, 62) / (n * ext * 1.0000001)
+    fixed = np.rint((x - lo) * fscale).astype(np.int64)
+    c = x[init].copy()
+    labels = P._assign_brute(x, c)
+    for _ in range(max_iter):
+        counts = np.bincount(labels, minlength=c.shape[0])
+        sums = np.zeros(c.shape, dtype=np.int64)
+        np.add.at(sums, labels, fixed)
+        full = counts > 0
+        c[full] = lo + (sums[full].astype(np.float64) / fscale) / counts[full, None]
+        empty = np.flatnonzero(~full)
+        if empty.size:
+            far = np.argsort(-((x - c[labels]) ** 2).sum(-1), kind="stable")
+            c[empty] = x[far[:empty.size]]
+        new = P._assign_brute(x, c)
+        same = np.array_equal(new, labels)
+        labels = new
+        if same and empty.size == 0:
+            break
+    return labels
+
+
+@pytest.mark.parametrize("d", [1, 2, 3])
+@pytest.mark.parametrize("n,bc", [(1001, 127), (1001, 128), (3001, 700)])
+@pytest.mark.parametrize("shape", ["even", "clumps", "one_cell"])
+def test_blocks_cell_walk_equals_lloyd(n, bc, d, shape):
+    """Around the block count from which points are assigned through the grid of
+    cells, on even points, on clumps with outliers far from them, and on points
+    that nearly all share one cell (where the exhaustive kernel takes over); two
+    equal starting points leave a cluster empty, so that it is re-seeded.  The
+    blocks equal those of the definition after 0, 1 and 11 iterations (the flags
+    of eight are read together).  Metric weights are powers of two, so the
+    scaled coordinates are exact."""
+    from paper_2410_04477_amd import api
+    g = W.rng(31 + d)
+    s = g.random((n, d))
+    if shape == "clumps":
+        s = g.random((9, d))[g.integers(0, 9, n)] + 0.01 * g.standard_normal((n, d))
+        s[:5] = 40.0 + 10.0 * g.random((5, d))
+    elif shape == "one_cell":
+        s *= 1e-3
+        s[-2:] = [[50.0] * d, [-50.0] * d]
+    w = [1.0, 1.0, 4.0][:d]
+    init = W.kmeans_init(n, bc, 3)
+    s[init[7]] = s[init[3]]
+    bperm = W.block_permutation(bc, 3)
+    for iters in (0, 1, 11):
+        perm, bp, it = api.blocks(torch.tensor(s, device=DEV), bc, torch.tensor(init, device=DEV),
+                                  torch.tensor(bperm, device=DEV), w, max_iter=iters)
+        perm_r, bp_r = P.order_blocks(_lloyd_fixed_point(s, np.array(w), init, iters), bperm)
+        assert it <= iters
+        np.testing.assert_array_equal(bp.cpu().numpy(), bp_r)
+        np.testing.assert_array_equal(perm.cpu().numpy(), perm_r)
