@@ -523,6 +523,17 @@ int vecchia_colsum(const float* X, int32_t M, int32_t N, int32_t ld, float* out,
 int vecchia_adam(float* param, const float* grad, float* m, float* v, int64_t n, double lr, double beta1,
                  double beta2, double eps, int64_t step, void* stream);
 
+/* vecchia_mlp_step: one training step of a three-layer ReLU network with BF16
+ * products: forward, mean squared error, backward and Adam, the operations of
+ * vecchia_gemm (use_bf16), vecchia_mse, vecchia_colsum and vecchia_adam in their
+ * order, in eight launches.  sizes[4]: layer widths; params / m / v: six device
+ * pointers each (weight (out, in), bias per layer), updated in place; loss_part as
+ * vecchia_mse; X: batch x sizes[0], target: batch x sizes[3]. */
+size_t vecchia_mlp_step_workspace_size(int32_t batch, const int32_t* sizes);
+int vecchia_mlp_step(const float* X, const float* target, int32_t batch, const int32_t* sizes, float* const* params,
+                     float* const* m, float* const* v, double* loss_part, int32_t nparts, double lr, double beta1,
+                     double beta2, double eps, int64_t step, void* workspace, size_t ws_bytes, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -73,6 +73,8 @@ SIGNATURES = {
     "vecchia_mse": (ctypes.c_int, [P, P, I32, P, P, I32, P]),
     "vecchia_colsum": (ctypes.c_int, [P, I32, I32, I32, P, P]),
     "vecchia_adam": (ctypes.c_int, [P, P, P, P, I64, D, D, D, D, I64, P]),
+    "vecchia_mlp_step_workspace_size": (SZ, [I32, P]),
+    "vecchia_mlp_step": (ctypes.c_int, [P, P, I32, P, P, P, P, P, I32, D, D, D, D, I64, P, SZ, P]),
     "vecchia_tile_config": (ctypes.c_int, [I32, I32, P, P]),
     "vecchia_plan_attach_aux": (ctypes.c_int, [P, P, SZ]),
     "vecchia_plan_destroy": (ctypes.c_int, [P]),

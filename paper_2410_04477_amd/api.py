@@ -379,6 +379,23 @@ def adam(param: torch.Tensor, grad: torch.Tensor, m: torch.Tensor, v: torch.Tens
                                  _stream(param.device)), "vecchia_adam")
 
 
+def mlp_step(X: torch.Tensor, target: torch.Tensor, sizes: Sequence[int], params: Sequence[torch.Tensor],
+             m: Sequence[torch.Tensor], v: Sequence[torch.Tensor], step: int, lr: float = 1e-3, beta1: float = 0.9,
+             beta2: float = 0.999, eps: float = 1e-8, nparts: int = 8) -> torch.Tensor:
+    """One training step of a three-layer ReLU network (vecchia_mlp_step); params,
+    m and v are updated in place.  Returns the loss parts."""
+    _dev_check(X, target, *params, *m, *v)
+    lib = L.lib()
+    n = (ctypes.c_int32 * 4)(*sizes)
+    batch = X.shape[0]
+    ptrs = [(ctypes.c_void_p * 6)(*[t.data_ptr() for t in ts]) for ts in (params, m, v)]
+    ws = torch.empty(int(lib.vecchia_mlp_step_workspace_size(batch, n)), dtype=torch.uint8, device=X.device)
+    part = torch.empty(nparts, dtype=torch.float64, device=X.device)
+    L.check(lib.vecchia_mlp_step(_p(X), _p(target), batch, n, *ptrs, _p(part), nparts, lr, beta1, beta2, eps, step,
+                                 _p(ws), ws.numel(), _stream(X.device)), "vecchia_mlp_step")
+    return part
+
+
 # ---------------------------------------------------------------- prediction
 
 

@@ -87,6 +87,10 @@ class MLP:
         return g
 
     def train_step(self, X: torch.Tensor, T: torch.Tensor, lr: float) -> torch.Tensor:
+        if self.bf16 and X.dim() == 2 and X.shape[1] == SIZES[0] and T.numel() == X.shape[0] * SIZES[3]:
+            # the same operations in one call
+            self.step_count += 1
+            return api.mlp_step(X, T, SIZES, self.params, self.m, self.v, self.step_count, lr)
         out, cache = self.forward(X)
         dout = torch.empty_like(out)
         part = api.mse(out, T, dout)

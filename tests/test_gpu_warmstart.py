@@ -31,6 +31,48 @@ def test_variogram_features_vs_oracle():
         np.testing.assert_allclose(feat[b], OLR.features(locs[b], y[b], nus[b]), rtol=1e-6, atol=1e-7)
 
 
+@pytest.mark.parametrize("nsets,nbins,k", [(1, 32, 257), (2, 32, 300), (8, 32, 600), (9, 32, 600), (5, 33, 600),
+                                           (7, 64, 600), (3, 5, 2)])
+def test_variogram_shared_design_vs_oracle(nsets, nbins, k):
+    """Sets that share a design go through the kernel in groups (of eight, or four
+    above 32 bins): group remainders, and lattice points, whose distances fall on
+    bin edges and on hmax.  FP64 sums of at most 1.8e5 positive terms in two
+    orders: 1e-12."""
+    from paper_2410_04477_amd import api
+    g = W.rng(50 + nsets)
+    locs = np.round(g.random((k, 2)) * 64) / 64 if k > 2 else np.array([[0.0, 0.0], [0.3, 0.4]])
+    y = g.standard_normal((nsets, k))
+    slots = torch.zeros(nsets, dtype=torch.int32, device=DEV)
+    _, gam = api.variogram(torch.tensor(locs, device=DEV), torch.tensor(y, device=DEV), slots, nbins, 0.5, 1,
+                           shared_design=True)
+    for b in range(nsets):
+        ref, _ = OLR.variogram(locs, y[b], nbins)
+        np.testing.assert_allclose(gam[b].cpu().numpy(), ref, rtol=1e-12, atol=0)
+
+
+@pytest.mark.parametrize("batch", [1, 16, 17, 130, 256])
+def test_mlp_step_equals_separate_calls(batch):
+    """The one-call training step does the operations of the separate calls in
+    their order: every parameter, moment and loss part is the same, bit for bit."""
+    from paper_2410_04477_amd import api
+    from paper_2410_04477_amd.warmstart import MLP
+    g = W.rng(60 + batch)
+    X = torch.tensor(np.abs(g.standard_normal((batch, 96))), dtype=torch.float32, device=DEV)
+    T = torch.tensor(g.standard_normal((batch, 3)), dtype=torch.float32, device=DEV)
+    a, b = MLP(5, DEV), MLP(5, DEV)
+    for step in (1, 2, 3):
+        part = a.train_step(X, T, 1e-3)
+        out, cache = b.forward(X)
+        dout = torch.empty_like(out)
+        part_b = api.mse(out, T, dout)
+        for p, gr, m, v in zip(b.params, b.backward(cache, dout), b.m, b.v):
+            api.adam(p, gr, m, v, step, 1e-3)
+        assert a.step_count == step
+        assert torch.equal(part, part_b)
+        for x, y in zip(a.params + a.m + a.v, b.params + b.m + b.v):
+            assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("ta,tb", [(False, False), (True, False), (False, True), (True, True)])
 @pytest.mark.parametrize("bf16", [True, False])
 def test_gemm_vs_oracle(ta, tb, bf16):
