@@ -510,7 +510,8 @@ hipError_t launch_mfma(int g, bool fp32, int mode, const AdjArgs& a, const Theta
                        hipStream_t s) {
   if (mode == 0) return fp32 ? launch_mfma_t<float, 0>(g, a, thp, grid, s) : launch_mfma_t<double, 0>(g, a, thp, grid, s);
   if (mode == 1) return fp32 ? launch_mfma_t<float, 1>(g, a, thp, grid, s) : launch_mfma_t<double, 1>(g, a, thp, grid, s);
-  return launch_mfma_t<double, 2>(g, a, thp, grid, s);
+  // coefficients: the one-wave kernels take the classes up to 10 tile rows
+  return g == 11 ? launch_mfma_g<double, 11, 2>(a, thp, grid, s) : hipErrorInvalidValue;
 }
 
 }  // namespace bv

@@ -64,7 +64,7 @@ struct AdjArgs {
 hipError_t launch_adjoint(int cfg, bool fp32, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
 size_t adjoint_lds_need(int cfg, bool fp32, int ldx);   // LDS bytes of one launch
 hipError_t launch_coefficients(int cfg, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
-// matrix-core engine: g tile rows (1..11); mode 0 value, 1 value + gradient, 2 coefficients (FP64)
+// matrix-core engine: g tile rows (1..11); mode 0 value, 1 value + gradient, 2 coefficients (FP64, g = 11)
 hipError_t launch_mfma(int g, bool fp32, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
 size_t mfma_lds_need(int g, bool fp32, int mode, int ldx);   // dynamic LDS bytes of one launch
 // one-wave matrix-core kernels (mode 0 value, 1 value + gradient); FP32 up to
@@ -109,6 +109,7 @@ hipError_t launch_wave_f32(int g, int mode, const AdjArgs& a, const ThetaPack& t
 hipError_t launch_wave_f64(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
 hipError_t launch_wave_f64_grad(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);    // mode 5
 hipError_t launch_wave_f64_pred(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);    // mode 4
+hipError_t launch_wave_f64_coef(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);    // mode 7, g <= 10
 hipError_t launch_wave_f64_tiles(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);   // mode 1
 hipError_t launch_wave_gen_f32(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
 hipError_t launch_wave_gen_f64(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);

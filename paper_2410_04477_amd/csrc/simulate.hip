@@ -1,12 +1,17 @@
 // Sequential Vecchia simulator (data generator for the synthetic workloads):
 // points in a given (random) order, point i drawn from N(c_i^T y_N(i), s_i)
 // given its nearest earlier points N(i).  The weights c_i and variances s_i
-// come from the adjoint kernel's coefficient mode (one workgroup per point,
-// FP64).  The recursion runs in passes: a point is drawn in the first pass in
-// which all of its neighbours were drawn in earlier passes, so each value is a
-// fixed function of the inputs (bit-for-bit reproducible).
+// come from the coefficient mode of the one-wave kernels (one wave per point,
+// FP64; the four-wave kernels above 10 tile rows).  The recursion runs as a data
+// flow: waves take the points in order and wait for the values of a point's
+// neighbours, which points taken earlier produce, so some wave can always go on.
+// Each value is a fixed function of the inputs (bit-for-bit reproducible).
+// Lists with a neighbour that is not earlier in the order run in passes instead: a
+// point is drawn in the first pass in which all of its neighbours were drawn in
+// earlier passes.
 #include <string.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "internal.hpp"
@@ -16,6 +21,102 @@ namespace bv {
 __global__ void unit_blocks_kernel(int* __restrict__ bp, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i <= n) bp[i] = i;
+}
+
+// Whether every neighbour comes earlier in the order (late is set where one does not).
+__global__ void sim_check_kernel(const int* __restrict__ nbr_ptr, const int* __restrict__ nbr_idx, int n,
+                                 int* __restrict__ late) {
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6), ln = threadIdx.x & 63;
+  if (i >= n) return;
+  const int o1 = nbr_ptr[i + 1];
+  bool bad = false;
+  for (int q = nbr_ptr[i] + ln; q < o1; q += 64) bad |= nbr_idx[q] < 0 || nbr_idx[q] >= i;
+  if (bad) *late = 1;
+}
+
+// A value that is not drawn yet: a NaN that no arithmetic produces (results are
+// written with NaNs made canonical).
+constexpr unsigned long long kNotDrawn = 0x7ff8c0de51a1d00dull;
+
+__global__ void sim_clear_kernel(unsigned long long* __restrict__ y, int64_t total, int* __restrict__ ticket, int nt) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < total) y[i] = kNotDrawn;
+  if (i < nt) ticket[i] = 0;
+}
+
+// One wave per point at a time, blockIdx.y the data set.  The point's weights and
+// neighbour indices are read while the wave waits; the neighbours' values are
+// polled where they are (value and readiness in one word, device-scope accesses,
+// as the producer may run on another XCD).  Every neighbour index is below the
+// point's, and points are taken in order, so the earliest unfinished point never
+// waits; the poll count is bounded all the same, and a wave that reaches the bound
+// says so and gives up.  20,000 points, 150 neighbours, 24 sets: the chain of
+// dependent points is about 1,200 long (94 ms as 1,216 passes over all points).
+constexpr int kSimPolls = 1 << 20;
+constexpr int kSimRegs = 4;   // neighbours per lane in registers (up to 256; more are read again)
+__global__ void __launch_bounds__(256)
+sim_flow_kernel(const int* __restrict__ nbr_ptr, const int* __restrict__ nbr_idx, const double* __restrict__ coef,
+                int64_t coef_stride, const double* __restrict__ cvar, const double* __restrict__ z,
+                unsigned long long* __restrict__ y, int n, int* __restrict__ ticket, int* __restrict__ stuck) {
+  const int ln = threadIdx.x & 63, t = blockIdx.y;
+  const double* cf = coef + (size_t)t * coef_stride;
+  unsigned long long* yt = y + (size_t)t * n;
+  // All lanes store the result.  With `if (lane == 0)` around the store as well as
+  // the ticket the compiler joined the end of one turn to the start of the next for
+  // the other lanes, which then took ticket 0 again and again and never left.
+  for (;;) {
+    int i = 0;
+    if (ln == 0) i = atomicAdd(&ticket[t], 1);
+    __builtin_amdgcn_wave_barrier();
+    i = __builtin_amdgcn_readfirstlane(i);
+    if (i >= n) return;
+    const int o0 = nbr_ptr[i], cnt = nbr_ptr[i + 1] - o0;
+    const double noise = sqrt(cvar[(size_t)t * n + i]) * z[(size_t)t * n + i];
+    double acc = 0.0;
+    bool ok = true;
+    for (int base = 0; base < cnt; base += 64 * kSimRegs) {
+      int idx[kSimRegs];
+      double w[kSimRegs];
+      unsigned long long v[kSimRegs];
+#pragma unroll
+      for (int k = 0; k < kSimRegs; ++k) {
+        const int q = base + 64 * k + ln;
+        idx[k] = q < cnt ? nbr_idx[o0 + q] : -1;
+        w[k] = q < cnt ? cf[o0 + q] : 0.0;
+        v[k] = q < cnt ? kNotDrawn : 0ull;
+      }
+      int polls = 0;
+      for (;;) {
+        bool wait = false;
+#pragma unroll
+        for (int k = 0; k < kSimRegs; ++k)
+          if (v[k] == kNotDrawn) {
+            v[k] = __hip_atomic_load(&yt[idx[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            wait |= v[k] == kNotDrawn;
+          }
+        if (!__any(wait)) break;
+        __builtin_amdgcn_s_sleep(1);
+        ++polls;
+        if (polls >= kSimPolls ||
+            (polls % 1024 == 0 && __hip_atomic_load(stuck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+          ok = false;
+          break;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kSimRegs; ++k)
+        if (idx[k] >= 0) acc += w[k] * __longlong_as_double((long long)v[k]);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if (!ok) {   // gives up, and with it every wave that waits
+      __hip_atomic_store(stuck, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    const double r = acc + noise;   // the same in every lane
+    const unsigned long long bits = r == r ? (unsigned long long)__double_as_longlong(r) : 0x7ff8000000000000ull;
+    __hip_atomic_store(&yt[i], bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 // grid.y runs over the data sets that share the design (same neighbour lists)
@@ -48,6 +149,7 @@ __global__ void sim_pass_kernel(const int* __restrict__ nbr_ptr, const int* __re
 using namespace bv;
 
 namespace {
+constexpr int kCoefMaxG = 10;   // tile rows of the one-wave coefficient kernels
 inline size_t al256s(size_t x) { return (x + 255) & ~(size_t)255; }
 struct SimLayout {
   size_t bp, cfg, sched, counts, stats, coef, cvar, flag, done, total;
@@ -153,10 +255,32 @@ extern "C" int vecchia_simulate(const double* locs_ord, int64_t n, int32_t d, co
     if (hc[c] == 0) continue;
     a.sched = sched + hoff[c];
     a.nsched = hc[c];
-    SCHECK(launch_mfma(c + 1, false, 2, a, thp, hc[c] * ntheta, s));
+    if (c + 1 <= kCoefMaxG) SCHECK(launch_wave_f64_coef(c + 1, a, thp, hc[c] * ntheta, s));
+    else SCHECK(launch_mfma(c + 1, false, 2, a, thp, hc[c] * ntheta, s));
+  }
+  int* done = at<int>(workspace, L.done);
+  // recursion: counts[0] a neighbour that is not earlier, [1] a wave that gave up,
+  // done[0 ..] the tickets of the sets
+  SCHECK(launch_fill_int(counts, 2, 0, s));
+  hipLaunchKernelGGL(sim_check_kernel, dim3((ni + 3) / 4), dim3(256), 0, s, nbr_ptr, nbr_idx, ni, counts);
+  SCHECK(hipGetLastError());
+  int flags[2];
+  SCHECK(hipMemcpyAsync(flags, counts, sizeof(flags), hipMemcpyDeviceToHost, s));
+  SCHECK(hipStreamSynchronize(s));
+  const int64_t ny = n * ntheta;   // (y over z: the passes read z[i] before they write y[i])
+  if (flags[0] == 0 && (y + ny <= z || z + ny <= y)) {
+    unsigned long long* yw = reinterpret_cast<unsigned long long*>(y);
+    hipLaunchKernelGGL(sim_clear_kernel, dim3((unsigned)((ny + 255) / 256)), dim3(256), 0, s, yw, ny, done, ntheta);
+    // about 2,048 waves in all, no more than a sixteenth of the points of a set
+    const int per = std::max(1, std::min(512 / ntheta, (ni + 63) / 64));
+    hipLaunchKernelGGL(sim_flow_kernel, dim3(per, ntheta), dim3(256), 0, s, nbr_ptr, nbr_idx, a.coef, (int64_t)hnnz,
+                       a.cvar, z, yw, ni, done, counts + 1);
+    SCHECK(hipGetLastError());
+    SCHECK(hipMemcpyAsync(flags, counts, sizeof(flags), hipMemcpyDeviceToHost, s));
+    SCHECK(hipStreamSynchronize(s));
+    return flags[1] ? VECCHIA_EHIP : VECCHIA_OK;
   }
   // recursion in passes
-  int* done = at<int>(workspace, L.done);
   int* ndone = done + (size_t)(n + 8) * ntheta;
   SCHECK(launch_fill_int(done, (ni + 8) * ntheta + 8, 0, s));
   const int target = ni * ntheta;

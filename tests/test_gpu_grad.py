@@ -245,6 +245,48 @@ def test_simulator_matches_oracle():
     np.testing.assert_allclose(y.cpu().numpy(), ref, rtol=1e-9, atol=1e-9)
 
 
+@pytest.mark.parametrize("n,m,sets", [(1, 5, 1), (40, 60, 2), (300, 14, 3), (700, 15, 24), (400, 142, 2), (400, 143, 1),
+                                      (400, 158, 2), (400, 174, 1)])
+def test_simulator_sizes_match_oracle(n, m, sets):
+    """Every tile count of the coefficient kernels (from 1 to 10 tile rows in one
+    wave, 11 in four), one and many data sets in one data flow.  Weights carry a
+    relative error of cond(K_N) u, below 1e-11 here (nugget 1e-3), and the
+    recursion keeps it: 1e-9."""
+    from paper_2410_04477_amd import api
+    from oracle.preprocess import point_neighbors
+    x = W.rng(90 + n + m).random((n, 2))
+    ptr, idx = point_neighbors(x, m)
+    z = W.rng(5).standard_normal((sets, n))
+    ths = [W.Theta(1.0 + 0.1 * k, 0.1, 1e-3, (0.5, 1.5, 2.5)[k % 3]) for k in range(sets)]
+    t = lambda a, dt: torch.tensor(np.asarray(a), dtype=dt, device=DEV)
+    ip = t(idx if len(idx) else np.zeros(1), torch.int32)
+    y = api.simulate(t(x, torch.float64), t(ptr, torch.int32), ip, ths, t(z, torch.float64)).cpu().numpy()
+    for k in range(sets):
+        ref = coracle.simulate(x, np.arange(n + 1), ptr, idx, ths[k], z[k])
+        np.testing.assert_allclose(y[k], ref, rtol=1e-9, atol=1e-9)
+
+
+def test_simulator_neighbour_that_is_not_earlier():
+    """A list without cycles whose neighbours are not all earlier still runs (in
+    passes), and equals the same design renumbered; a cycle is refused."""
+    from paper_2410_04477_amd import api
+    from paper_2410_04477_amd._lib import VecchiaError
+    n, th = 60, W.Theta(1.0, 0.2, 1e-2, 1.5)
+    x = W.rng(3).random((n, 2))
+    z = W.standard_normal(n, 4)
+    t = lambda a, dt: torch.tensor(np.ascontiguousarray(a), dtype=dt, device=DEV)
+    run = lambda xs, p, i, zs: api.simulate(t(xs, torch.float64), t(p, torch.int32), t(i, torch.int32), th,
+                                            t(zs, torch.float64)).cpu().numpy()
+    ptr = np.arange(n + 1) - 1
+    ptr[0] = 0
+    fwd = run(x, ptr, np.arange(n - 1), z)              # point i given point i - 1
+    rptr = np.minimum(np.arange(n + 1), n - 1)          # the same chain numbered backwards
+    back = run(x[::-1], rptr, np.arange(1, n), z[::-1])
+    np.testing.assert_allclose(back[::-1], fwd, rtol=1e-12, atol=1e-12)
+    with pytest.raises(VecchiaError):
+        run(x[:2], np.array([0, 1, 2]), np.array([1, 0]), z[:2])
+
+
 def test_mle_recovers_parameters_and_beats_start():
     from paper_2410_04477_amd import mle
     th = W.Theta(1.5, 0.08, 0.01, 1.5)
