@@ -109,8 +109,8 @@ __device__ inline void bessel_k_pair_quad(double x, double mu, double& k_mu, dou
 // three-term recurrence K_(v+1) = K_(v-1) + (2 v / x) K_v, which is stable
 // upwards for K.  Also returns g = 2^(1-nu)/Gamma(nu) x^(nu+1) K_(nu-1)(x),
 // from d/dx [x^nu K_nu(x)] = -x^nu K_(nu-1)(x): d rho(h/range) / d range =
-// g / range.  Not inlined: its loops would otherwise be copied into every
-// generation site.
+// g / range.  Not inlined: the kernels call it only for distances outside the
+// range of bessel4 below.
 __device__ __noinline__ inline void matern_general(double x, const BesselOrder& o, double* rho, double* g) {
   if (!(x > 1e-140)) {   // a coincident pair (distance<double> gives 1e-150)
     *rho = 1.0;
@@ -282,40 +282,6 @@ struct MaternCoef {
   }
 };
 
-// The correlation a kernel generates: closed forms (GEN = false), or the
-// Bessel form for any nu (GEN = true; FP64 evaluation rounded to T).
-template <typename T, bool GEN> struct MaternF;
-template <typename T> struct MaternF<T, false> : MaternCoef<T> {
-  __device__ __forceinline__ explicit MaternF(const ThetaDev& t) : MaternCoef<T>(t.nu_code) {}
-};
-template <typename T> struct MaternF<T, true> {
-  const ThetaDev& t;
-  __device__ __forceinline__ explicit MaternF(const ThetaDev& th) : t(th) {}
-  __device__ __forceinline__ T rho(T x) const {
-    double r, g;
-    matern_general((double)x, t.bes, &r, &g);
-    return T(r);
-  }
-  __device__ __forceinline__ void rho_drange(T x, T inv_range, T& r, T& dr) const {
-    double rr, g;
-    matern_general((double)x, t.bes, &rr, &g);
-    r = T(rr);
-    dr = T(g) * inv_range;
-  }
-  __device__ __forceinline__ T drange(T x, T inv_range) const {
-    double rr, g;
-    matern_general((double)x, t.bes, &rr, &g);
-    return T(g) * inv_range;
-  }
-  // d rho / d range and d rho / d nu (the derivative in nu by quadrature)
-  __device__ __forceinline__ void drange_dnu(T x, T inv_range, T& dr, T& dn) const {
-    double rr, g, d;
-    matern_general_dnu((double)x, t.bes, &rr, &g, &d);
-    dr = T(g) * inv_range;
-    dn = T(d);
-  }
-};
-
 // 1 / sqrt(x) in FP64, 0 < x < inf normal: the hardware estimate y (2^-24) and one
 // third-order step, y + y e (1/2 + 3/8 e) with e = 1 - x y^2: 1.4e-16 relative
 // at most (1 / sqrt(x) through the library: 1.7e-16), 5 dependent operations
@@ -395,6 +361,156 @@ __device__ __forceinline__ void distance_exp2neg4(const float (&dx)[4], const fl
     u[r] = distance<float>(dx[r], dy[r], dz[r]);
     w[r] = exp2neg<float>(u[r]);
   }
+}
+
+// ---- Bessel form of four pairs at once ---------------------------------------
+// K_v(x) = int_0^inf exp(-x cosh t) cosh(v t) dt by the trapezoidal rule with the
+// fixed step h = 1/6 for kBesselLo <= x <= kBesselMid, and h = 1/12 up to kBesselHi:
+// the discretisation error, about exp(x - pi^2 / h), is below 1e-16 there, the
+// rounding error of the sums at most 1.2e-15.  With a fixed step cosh t,
+// cosh(mu t), cosh((mu + 1) t) and t times their sinh depend on the node alone:
+// a workgroup forms them once, and a node costs one exponential and two products
+// (four with d / d nu).  12 to 50 nodes for the distances of neighbouring points,
+// 111 at x = 1e-6.  Rows kBesselNodes on are the nodes halfway, as far as
+// x > kBesselMid needs them (exp(-x (cosh t - 1)) < 1e-20 past the last).
+constexpr int kBesselNodes = 128, kBesselHalf = 14;
+constexpr int kBesselCols = 6;   // cosh t, h cosh(mu t), h cosh((mu + 1) t), h t sinh(mu t), h t sinh((mu + 1) t), a constant
+constexpr double kBesselStep = 1.0 / 6.0, kBesselLo = 6e-8, kBesselMid = 16.0, kBesselHi = 72.0;
+constexpr int kBesselBytes = (kBesselNodes + kBesselHalf) * kBesselCols * (int)sizeof(double);
+typedef const __attribute__((address_space(3))) double LdsDouble;
+
+// The table of one order by the 64 lanes of a wave; the caller orders the LDS accesses.
+__device__ inline void bessel_table(double* tab, const BesselOrder& o, int ln) {
+  for (int k = ln; k < kBesselNodes + kBesselHalf; k += 64) {
+    const double t = (k < kBesselNodes ? k : k - kBesselNodes + 0.5) * kBesselStep;
+    const double w = k == 0 ? 0.5 * kBesselStep : kBesselStep;
+    const double e = exp(t), em = exp(o.mu * t);
+    const double p = em * e, ei = 1.0 / e, emi = 1.0 / em, pi = 1.0 / p;
+    double* row = tab + k * kBesselCols;
+    row[0] = 0.5 * (e + ei);
+    row[1] = w * 0.5 * (em + emi);
+    row[2] = w * 0.5 * (p + pi);
+    row[3] = w * t * 0.5 * (em - emi);
+    row[4] = w * t * 0.5 * (p - pi);
+    row[5] = k == 0 ? o.mu : k == 1 ? (double)o.n : k == 2 ? o.lognorm : k == 3 ? o.dlognorm
+           : k == 4 ? o.gplus : k == 5 ? o.gminus : k == 6 ? o.gam1 : k == 7 ? o.gam2 : o.mu_pi_csc;
+  }
+}
+
+// The functions of four distances: WHAT 0 rho, 1 g (as matern_general), 2 g and
+// d rho / d nu.  One copy for all tiles of a kernel (a copy per tile made the
+// kernels 90 to 460 KB); the results come back in registers.  Bound by the FP64
+// operations of the exponentials: 2,000 blocks, m = 30, d l / d range and d l / d nu
+// 520 us, one distance at a time with its own step (about 110 nodes at
+// x = 1e-4, all weights recomputed, arrays in scratch) 1,112 us.  Outside
+// [kBesselLo, kBesselHi] the functions above are called, lane by lane.
+typedef double BesselOut __attribute__((ext_vector_type(8)));
+typedef double Bessel4 __attribute__((ext_vector_type(4)));
+template <int WHAT>
+__device__ __noinline__ inline BesselOut bessel4(Bessel4 x, LdsDouble* tab) {
+  constexpr bool DNU = WHAT == 2;
+  const int order = (int)tab[kBesselCols + 5];
+  const double mu = tab[5], lognorm = tab[2 * kBesselCols + 5], dlognorm = tab[3 * kBesselCols + 5];
+  double u[4], k0[4], k1[4], d0[4], d1[4];
+  bool rare = false, half = false;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const bool in = x[r] >= kBesselLo && x[r] <= kBesselHi;
+    rare |= !in & (x[r] > 1e-140);
+    half |= in & (x[r] > kBesselMid);
+    u[r] = (in ? x[r] : 1.0) * kLog2E;
+    k0[r] = k1[r] = d0[r] = d1[r] = 0.0;
+  }
+  auto node = [&](LdsDouble* row) __attribute__((always_inline)) {
+    const double ch = row[0], c0 = row[1], c1 = row[2], s0 = row[3], s1 = row[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double e = exp2neg<double>(u[r] * ch);
+      k0[r] = __builtin_fma(e, c0, k0[r]);
+      k1[r] = __builtin_fma(e, c1, k1[r]);
+      if (DNU) {
+        d0[r] = __builtin_fma(e, s0, d0[r]);
+        d1[r] = __builtin_fma(e, s1, d1[r]);
+      }
+    }
+  };
+  if (__any(half)) {
+    // the nodes halfway first: their sums count for x > kBesselMid only, and both
+    // sets then weigh one half
+#pragma nounroll
+    for (int k = kBesselNodes; k < kBesselNodes + kBesselHalf; ++k) node(tab + k * kBesselCols);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool take = u[r] > kBesselMid * kLog2E;
+      k0[r] = take ? k0[r] : 0.0;
+      k1[r] = take ? k1[r] : 0.0;
+      d0[r] = take ? d0[r] : 0.0;
+      d1[r] = take ? d1[r] : 0.0;
+    }
+  }
+#pragma nounroll
+  for (int k = 0; k < kBesselNodes; k += 4) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) node(tab + (k + q) * kBesselCols);
+    // past t = 1 t sinh((mu + 1) t) exceeds a third of every other weight of a node
+    const double ch = tab[(k + 3) * kBesselCols], s1 = tab[(k + 3) * kBesselCols + 4];
+    bool more = k < 4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) more |= exp2neg<double>(u[r] * ch) * s1 > 1e-19 * k1[r];
+    if (!__any(more)) break;
+  }
+  const double nu = mu + order;
+  BesselOut out = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const double w = u[r] > kBesselMid * kLog2E ? 0.5 : 1.0;
+    const double z = u[r] * kLn2, zi = 1.0 / z;
+    double klo = k0[r], khi = k1[r], dlo = d0[r], dhi = d1[r];   // K_(nu-1), K_nu, their derivatives in nu
+    if (order == 0) {
+      klo = k1[r] - (2.0 * mu * zi) * k0[r];
+      khi = k0[r];
+      dhi = d0[r];
+    }
+    for (int v = 1; v < order; ++v) {
+      const double f = 2.0 * (mu + v) * zi;
+      const double kn = klo + f * khi;
+      if (DNU) {
+        const double dnx = dlo + f * dhi + (2.0 * zi) * khi;
+        dlo = dhi;
+        dhi = dnx;
+      }
+      klo = khi;
+      khi = kn;
+    }
+    const double logx = log(z);
+    const double c = w * exp(lognorm + nu * logx);
+    const bool at0 = !(x[r] > 1e-140);   // a coincident pair (distance<double> gives 1e-150)
+    if (WHAT == 0) out[r] = at0 ? 1.0 : c * khi;
+    if (WHAT >= 1) out[r] = at0 ? 0.0 : c * z * klo;
+    if (DNU) out[r + 4] = at0 ? 0.0 : c * (khi * (logx + dlognorm) + dhi);
+  }
+  if (__any(rare)) {
+    BesselOrder o;
+    o.mu = mu;
+    o.n = order;
+    o.lognorm = lognorm;
+    o.dlognorm = dlognorm;
+    o.gplus = tab[4 * kBesselCols + 5];
+    o.gminus = tab[5 * kBesselCols + 5];
+    o.gam1 = tab[6 * kBesselCols + 5];
+    o.gam2 = tab[7 * kBesselCols + 5];
+    o.mu_pi_csc = tab[8 * kBesselCols + 5];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (x[r] > 1e-140 && !(x[r] >= kBesselLo && x[r] <= kBesselHi)) {
+        double rho, g, dn = 0.0;
+        if (DNU) matern_general_dnu(x[r], o, &rho, &g, &dn);
+        else matern_general(x[r], o, &rho, &g);
+        out[r] = WHAT == 0 ? rho : g;
+        if (DNU) out[r + 4] = dn;
+      }
+  }
+  return out;
 }
 
 // rho and x * d rho / d x * (-1) / range, i.e. d rho(h/range) / d range.

@@ -134,6 +134,11 @@ __host__ __device__ constexpr int wave_lds_elems(int G, int mode) {
          (mode == 5 ? 16 * G : 0);
 }
 
+// bytes before the Bessel form's table in the LDS
+__host__ __device__ constexpr int wave_table_offset(int elem, int G, int mode) {
+  return (elem * wave_lds_elems(G, mode) + 15) / 16 * 16;
+}
+
 // Waves per SIMD that a kernel's registers have to allow (512 per lane and SIMD).
 // A wave's matrix-core and vector instructions share the FP32 / FP64 units (one
 // wave that mixes them takes the sum of their times), so more waves only hide
@@ -146,7 +151,9 @@ template <typename T, int G, int MODE, bool GEN>
 constexpr int wave_min_waves() {
   if (MODE == 6) return 2;
   if (sizeof(T) == 8) {
-    if (GEN || MODE == 1 || MODE == 3) return 1;
+    if (MODE == 1 || MODE == 3) return 1;
+    // Bessel form: the call's own registers, so two waves where the tiles leave room without scratch
+    if (GEN) return G <= 3 || (G == 4 && MODE != 5) ? 2 : 1;
     if (MODE == 5) return G <= 5 ? 2 : 1;
     if (MODE == 7) return G <= 3 ? 3 : G <= 6 ? 2 : 1;
     return G <= 2 ? 4 : G <= 4 ? 3 : G <= 6 ? 2 : 1;
@@ -268,7 +275,14 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   T* Lg = reinterpret_cast<T*>(a.tiles) + (size_t)(wi - a.item_base) * SLOT;
   double acc_ll = 0.0;
   int flag = 0;
-  const MaternF<T, GEN> mc(th);
+  const MaternCoef<T> mc(th.nu_code);   // closed forms
+  // Bessel form: the table of this order, after the rest of the LDS
+  double* const table = reinterpret_cast<double*>(smem + wave_table_offset(sizeof(T), G, MODE));
+  LdsDouble* const btab = (LdsDouble*)table;
+  if constexpr (GEN) {
+    bessel_table(table, th.bes, ln);
+    wave_lds_sync();
+  }
   acc_t acc[NT];   // the bordered matrix, then its factor (unused by MODE 3)
   if constexpr (MODE != 3) {   // MODE 3 starts from the factor tiles of a MODE 2 or 6 launch
 
@@ -304,12 +318,20 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
       dy[r] = ri[r][1] - sj1;
       dz[r] = ri[r][2] - sj2;
     }
-    if constexpr (!GEN) distance_exp2neg4<STAGED>(dx, dy, dz, u, e);
+    BesselOut bes;
+    if constexpr (!GEN) {
+      distance_exp2neg4<STAGED>(dx, dy, dz, u, e);
+    } else {
+      Bessel4 x;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[r] = (double)distance<T>(dx[r], dy[r], dz[r]);
+      bes = bessel4<0>(x, btab);
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       // the tiles hold the negated matrix (updates add L L^T)
       T v;
-      if constexpr (GEN) v = -(sig2 * mc.rho(distance<T>(dx[r], dy[r], dz[r])));
+      if constexpr (GEN) v = -(sig2 * T(bes[r]));
       else v = mc.neg_cov_log2(u[r], e[r], ns0, ns1, ns2);
       if constexpr (I == J) v -= (M::row(lg, r) == lr) ? nug : T(0);   // the nugget: same-index pairs only
       acc[tix(I, J)][r] = v;
@@ -336,9 +358,10 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
     // Where the tiles outgrow the VGPRs the finished tile goes to the accumulator
     // registers now, so that the generated values do not pile up until the first
     // update: by D = 0 * 0 + C, or (the FP64 value kernels, whose first 32 tiles
-    // fill the accumulator registers) by asking for the move itself.
+    // fill the accumulator registers) by asking for the move itself; not with the
+    // Bessel form, where tiles asked for like this did not survive the calls.
     constexpr bool ONE = sizeof(T) == 8 && wave_min_waves<T, G, MODE, GEN>() == 1;
-    if constexpr (ONE && MODE == 0) {
+    if constexpr (ONE && MODE == 0 && !GEN) {
       if constexpr (tix(I, J) < 32) asm volatile("" : "+a"(acc[tix(I, J)]));
     } else if constexpr (sizeof(T) == 8 ? ONE || (LEFT && G == 10) : !(G <= 9 && (MODE == 5 || MODE == 2))) {
       acc[tix(I, J)] = M::op(T(0), T(0), acc[tix(I, J)]);
@@ -987,18 +1010,19 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
           dy[r] = ri[r][1] - sj1;
           dz[r] = ri[r][2] - sj2;
         }
-        if constexpr (!GEN) distance_exp2neg4<STAGED>(dx, dy, dz, u, e);
+        BesselOut bes;   // g of the four, then their d rho / d nu
+        if constexpr (!GEN) {
+          distance_exp2neg4<STAGED>(dx, dy, dz, u, e);
+        } else {
+          Bessel4 x;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x[r] = (double)distance<T>(dx[r], dy[r], dz[r]);
+          bes = want_nu ? bessel4<2>(x, btab) : bessel4<1>(x, btab);
+        }
         auto entry = [&](int r) __attribute__((always_inline)) {
           if constexpr (GEN) {
-            const T x = distance<T>(dx[r], dy[r], dz[r]);
-            if (want_nu) {
-              T dr, dn;
-              mc.drange_dnu(x, irange, dr, dn);
-              s1 += c[r] * dr;
-              s3 += c[r] * dn;
-            } else {
-              s1 += c[r] * mc.drange(x, irange);
-            }
+            s1 += c[r] * (T(bes[r]) * irange);
+            if (want_nu) s3 += c[r] * T(bes[r + 4]);
           } else {
             s1 += c[r] * mc.drange_log2(u[r], e[r], dh0, dh1, dh2);
           }
@@ -1298,7 +1322,8 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
 
 template <typename T, int G, int MODE, bool GEN>
 static hipError_t launch_wave_g(const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s) {
-  const size_t lds = sizeof(T) * (size_t)wave_lds_elems(G, MODE);
+  const size_t lds = GEN ? (size_t)wave_table_offset(sizeof(T), G, MODE) + kBesselBytes
+                         : sizeof(T) * (size_t)wave_lds_elems(G, MODE);
   hipLaunchKernelGGL((bv_wave_kernel<T, G, MODE, GEN>), dim3(grid), dim3(64), lds, s, a, thp);
   return hipGetLastError();
 }

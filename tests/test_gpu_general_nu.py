@@ -42,6 +42,28 @@ def test_correlation_through_one_neighbour_prediction(nu):
     np.testing.assert_allclose(var.cpu().numpy(), 1.0 - ref * ref, rtol=1e-10, atol=1e-13)
 
 
+@pytest.mark.parametrize("nu", [0.05, 0.5001, 1.0, 2.3, 10.0])
+def test_correlation_at_the_edges_of_the_quadrature(nu):
+    """Distances around the ends of the fixed-step rules (6e-8, 16 and 72 range
+    units), beyond both and 0, four different ranges in the lanes of one wave:
+    the conditional mean of one neighbour's value is rho, against scipy's K_nu."""
+    from paper_2410_04477_amd import api
+    th = W.Theta(1.0, 1.0, 0.0, nu)
+    x = np.concatenate([[1e-9, 5.9e-8, 6e-8, 6.1e-8, 1e-6, 15.9, 16.0, 16.1, 30.0, 71.9, 72.1, 90.0], np.geomspace(1e-7, 80.0, 21)])
+    # block i: new points at every distance x from the one observation
+    nb = 7
+    s_obs = np.stack([np.arange(nb) * 1e4, np.zeros(nb)], 1)
+    s_new = np.stack([np.repeat(s_obs[:, 0], x.size), np.tile(x, nb)], 1)
+    s_new[::x.size, 1] = 0.0     # and one at the observation itself
+    bp = np.arange(nb + 1) * x.size
+    plan = api.Plan(_t(bp, torch.int32), _t(np.arange(nb + 1), torch.int32), s_new.shape[0], 1, "mfma", predict=True)
+    mean, _, cov = api.predict(plan, _t(s_obs), _t(np.ones(nb)), _t(s_new), _t(np.arange(nb), torch.int32), th, True)
+    xs = np.tile(x, nb)
+    xs[::x.size] = 0.0
+    ref = np.where(xs > 0, matern.rho_general(np.maximum(xs, 1e-300), nu), 1.0)
+    np.testing.assert_allclose(mean.cpu().numpy(), ref, rtol=1e-12, atol=1e-300)
+
+
 def _gpu_ll(pb, thetas, precision, grad=False):
     from paper_2410_04477_amd import api
     plan = api.Plan(_t(pb["block_ptr"], torch.int32), _t(pb["nbr_ptr"], torch.int32), pb["n"], len(thetas))
