@@ -393,7 +393,7 @@ def bench_large_blocks(w, steps, dev):
     t_pre = time.perf_counter() - t0
     plan = model.plan
     classes = plan.buckets()
-    ql = [q for q in range(len(classes)) if plan.class_kernel(q, "fp64", False).startswith("bv_large_kernel")]
+    ql = [q for q in range(len(classes)) if plan.class_kernel(q, "fp64", False).startswith("bv_large")]
     assert len(ql) == 1 and int(plan.c.nlarge) > 0, "the workload has no blocks above the one-wave limit"
     ql = ql[0]
     sched = plan.schedule().cpu().numpy()

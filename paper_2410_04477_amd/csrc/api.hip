@@ -385,7 +385,8 @@ extern "C" int vecchia_plan_class_kernel(const vecchia_plan* plan, int32_t q, in
   const int mode = class_wave_mode(plan, q, fp32, with_grad != 0);
   int n;
   if (plan->bucket_cfg[q] == kLargeCfg)
-    n = snprintf(name, (size_t)cap, "bv_large_kernel<%s>", t);
+    n = fp32 || with_grad ? snprintf(name, (size_t)cap, "bv_large_kernel<%s>", t)
+                          : snprintf(name, (size_t)cap, "bv_large_f64_kernel");
   else if (mode == 23 || mode == 63)
     n = snprintf(name, (size_t)cap, "bv_wave_kernel<%s,%d,%d>+bv_wave_kernel<%s,%d,3>", t, g, mode / 10, t, g);
   else if (mode >= 0)

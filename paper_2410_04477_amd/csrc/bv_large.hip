@@ -14,6 +14,8 @@
 // tile row by tile row (16 x 16 triangular solves, MFMA updates of the rows
 // above) and contracts W with d K / d range regenerated from the staged
 // coordinates, as the one-wave kernels do.
+// FP64 values have a kernel of their own (bv_large_f64.hip); this one runs the
+// FP32 bulk and holds the FP64 gradient.
 #include "internal.hpp"
 
 namespace bv {
@@ -464,7 +466,7 @@ hipError_t launch_large(bool fp32, bool grad, const LargeArgs& a, const ThetaPac
     else hipLaunchKernelGGL((bv_large_kernel<float, false>), dim3(grid), dim3(256), 0, s, a, thp);
   } else {
     if (grad) hipLaunchKernelGGL((bv_large_kernel<double, true>), dim3(grid), dim3(256), 0, s, a, thp);
-    else hipLaunchKernelGGL((bv_large_kernel<double, false>), dim3(grid), dim3(256), 0, s, a, thp);
+    else return launch_large_f64(a, thp, grid, s);
   }
   return hipGetLastError();
 }

@@ -143,6 +143,7 @@ constexpr size_t kLargeSlotCap = (size_t)4 << 30;
 // right-hand sides and 3 P staged coordinates, P = 16 ceil((p_max + 1) / 16)
 size_t large_slot_elems(int pmax, int lmax);
 hipError_t launch_large(bool fp32, bool grad, const LargeArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
+hipError_t launch_large_f64(const LargeArgs& a, const ThetaPack& thp, int grid, hipStream_t s);   // FP64 value
 
 // leading dimension of the LDS right-hand sides for l_max (matrix-core engine)
 inline int mfma_ldx(int nr_max) { return 16 * ((nr_max + 15) / 16) + 1; }
