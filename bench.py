@@ -38,7 +38,7 @@ def log(msg: str) -> None:
 def kernel_source_sha() -> str:
     h = hashlib.sha256()
     for f in ("wave_kernel.hpp", "bv_wave_f32.hip", "bv_wave_f64.hip", "bv_wave_f64_grad.hip",
-              "bv_wave_f64_coef.hip", "bv_wave_f64_pred.hip", "bv_wave_f64_tiles.hip", "bv_mfma.hip", "bv_adjoint.hip",
+              "bv_wave_f64_coef.hip", "bv_wave_f64_value.hip", "wave_rows.hpp", "bv_wave_f64_pred.hip", "bv_wave_f64_tiles.hip", "bv_mfma.hip", "bv_adjoint.hip",
               "bv_forward.hip", "common.hpp", "internal.hpp", "api.hip"):
         with open(os.path.join(ROOT, "paper_2410_04477_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())

@@ -109,7 +109,8 @@ hipError_t launch_wave_f32(int g, int mode, const AdjArgs& a, const ThetaPack& t
 hipError_t launch_wave_f64(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
 hipError_t launch_wave_f64_grad(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);    // mode 5
 hipError_t launch_wave_f64_pred(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);    // mode 4
-hipError_t launch_wave_f64_coef(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);    // mode 7, g <= 10
+hipError_t launch_rows_value(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);       // mode 0, g = 7 .. 10
+hipError_t launch_wave_f64_coef(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);    // simulator, g <= 10
 hipError_t launch_wave_f64_tiles(int g, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);   // mode 1
 hipError_t launch_wave_gen_f32(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);
 hipError_t launch_wave_gen_f64(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s);

@@ -123,9 +123,7 @@ __host__ __device__ constexpr int wave_lds_elems(int G, int mode) {
   // (P x (wave_chunk(G) + 1), plus 32 elements that reads of the last row's
   // unused columns may touch), which also holds the G staged diagonal tiles
   // before the first chunk
-  // (mode 5 keeps the border row w of the factor after that, 16 G elements, and
-  // so does mode 7, whose one right-hand side fills one column of 16)
-  if (mode == 7) return 3 * 16 * G + wave_max(wave_max(4 * (16 * G + 16), 256) + 3 * 16 * G, 16 * G * 17 + 32) + 16 * G;
+  // (mode 5 keeps the border row w of the factor after that, 16 G elements)
   return 3 * 16 * G + wave_max(4 * (16 * G + (mode == 2 || mode == 5 || mode == 6 ? 16 : 0)) + 3 * 16 * G,
                                mode == 0 || mode == 2 || mode == 4 || mode == 6 ? 0
                                : (16 * (wave_chunk(G) + 1) > kStageStride
@@ -155,7 +153,6 @@ constexpr int wave_min_waves() {
     // Bessel form: the call's own registers, so two waves where the tiles leave room without scratch
     if (GEN) return G <= 3 || (G == 4 && MODE != 5) ? 2 : 1;
     if (MODE == 5) return G <= 5 ? 2 : 1;
-    if (MODE == 7) return G <= 3 ? 3 : G <= 6 ? 2 : 1;
     return G <= 2 ? 4 : G <= 4 ? 3 : G <= 6 ? 2 : 1;
   }
   if (MODE == 0 && G <= 5) return 5;
@@ -178,11 +175,8 @@ constexpr int wave_min_waves() {
 // buffer), factored in its four panels and stored, so that only one tile
 // column is in the registers at a time (FP64 classes above G = 9, whose tiles
 // exceed the register file); mode 3 takes the adjoint from its tiles.
-// 7 (FP64) conditional-mean weights and conditional variance of one point given
-// its neighbours (the simulator): the block is the point, row m of the joint
-// matrix; its row of the factor is w = L_N^-1 k and its pivot the variance; the
-// factor stays in the registers as in mode 5 and the weights are L_N^-T w, one
-// right-hand side.
+// (The FP64 value above G = 6 and the simulator's weights have a kernel of their
+// own, wave_rows.hpp.)
 // GEN: covariances by the Bessel form for any nu instead of the closed forms.
 template <typename T, int G, int MODE, bool GEN>
 __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wave_kernel(AdjArgs a, ThetaPack thp) {
@@ -205,13 +199,13 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   // MODE 5 appends 16 rows to the panel (the identity rows whose elimination
   // gives the inverse of each diagonal tile of the factor)
   constexpr bool LEFT = MODE == 6;                // left-looking by tile columns
-  constexpr bool INREG = MODE == 5 || MODE == 7;   // factor kept in the registers
+  constexpr bool INREG = MODE == 5;                // factor kept in the registers
   constexpr bool EINV = INREG || MODE == 2 || LEFT;   // diagonal inverses formed during the factorisation
   constexpr int PS = EINV ? P + 16 : P;            // panel column stride
   // the panel, also the scratch of the 16 x 16 transposition, which the panel of
   // G <= 2 does not hold (KNOWN FAULT, left as it was: in modes 2, 5 and 6 it then
   // overwrites the pivots, and the value and gradient of classes G <= 2 come out NaN)
-  constexpr int PANEL = MODE == 7 ? wave_max(4 * PS, 256) : 4 * PS;
+  constexpr int PANEL = 4 * PS;
   static_assert(3 * P + PANEL + 3 * P <= wave_lds_elems(G, MODE), "factorisation LDS");
   T* sy = work + PANEL;                // border row y_J
   T* sdk = sy + P;                     // pivots d_k
@@ -255,7 +249,7 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
       } else {
         const int g = (i < m) ? a.nbr_idx[n0 + i] : (b0 + i - m);
         src = a.locs + (size_t)g * a.d;
-        if (MODE != 3 && MODE != 7) sy[i] = T(a.y[g]);
+        if (MODE != 3) sy[i] = T(a.y[g]);
       }
       for (int k = 0; k < 3; ++k) {
         T v = k < a.d ? T((src[k] - org[k]) * (th.inv_scale[k] * UNIT)) : T(0);
@@ -346,7 +340,7 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
         const T v = acc[tix(I, J)][r];
         acc[tix(I, J)][r] = real_row(i) & real_row(j) ? v : (i == j) ? T(-1) : T(0);
       }
-      if (MODE != 7 && I == (p >> 4)) {  // border row p: y_J
+      if (I == (p >> 4)) {  // border row p: y_J
         const T yb = sy[j];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -607,11 +601,10 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
     // above the block, and right of the diagonal in it, L is zero (columns at and
     // beyond p have entries in rows from p on only, which nothing reads)
     if (lr < k0 - 16 * K + lg) v[K] = T(0);
-    // the border row's entries of the four columns (mode 7: the point's row)
-    const int brow = MODE == 7 ? m : p;
+    // the border row's entries of the four columns
     T w = T(0);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) w += pan[brow * 4 + c] * z[c];
+    for (int c = 0; c < 4; ++c) w += pan[p * 4 + c] * z[c];
     if (lr == 0) swk[k0 + lg] = w;
   };
 
@@ -873,7 +866,6 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   }
 
   // ---- log-determinant, quadratic form and pivot guard (FP64) -----------------
-  if constexpr (MODE != 7) {
   const double guard = a.fp32_guard == 2 ? INFINITY
       : a.fp32_guard ? fmax(0.5 * th.nugget, (double)p * 1.1920928955078125e-07 * (th.sigma2 + th.nugget))
       : 0.0;
@@ -892,7 +884,6 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   for (int off = 32; off > 0; off >>= 1) {
     acc_ll += __shfl_down(acc_ll, off, 64);
     flag |= __shfl_down(flag, off, 64);
-  }
   }
   if (MODE == 0 || MODE == 2 || MODE == 6) {
     if (ln == 0) {
@@ -921,14 +912,14 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
     flag = a.flag[o];   // written by the factorisation launch
   }
 
-  constexpr int CH = MODE == 7 ? 16 : wave_chunk(G);   // right-hand sides per pass
+  constexpr int CH = wave_chunk(G);   // right-hand sides per pass
   constexpr int NQ = (CH + 15) / 16;             // 16-column tiles of one pass
   constexpr int LDX = CH + 1;
   // with CH < 32 the second 16-column tile is partly outside a row: its reads
   // there are harmless (other columns of the MFMA results), its writes masked
   auto colok = [&](int q) __attribute__((always_inline)) { return (q + 1) * 16 <= CH || q * 16 + lr < CH; };
   constexpr int GM = G > 1 ? G - 1 : 1;   // tile rows above a diagonal step, at most
-  const int nr = MODE == 7 ? 1 : l + 2;
+  const int nr = l + 2;
   const int Gp = (p + 15) >> 4;
   T* X = work;   // X[row * LDX + col], one chunk of right-hand sides
   // clears X (and the 32 elements after it) with 16-byte stores
@@ -1055,7 +1046,6 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
     // LDS record to LDS past the right-hand sides (which overwrite the record)
     T* sw = work + wave_max(PANEL + 3 * P, P * LDX + 32);
     static_assert(3 * P + wave_max(PANEL + 3 * P, P * LDX + 32) + P <= wave_lds_elems(G, MODE), "LDS of w");
-    const T var = MODE == 7 ? sdk[m] : T(0);   // the point's pivot
     for (int j = ln; j < P; j += 64) {
       const T w = j < p ? swk[j] : T(0);
       sw[j] = w;
@@ -1067,16 +1057,12 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
     // columns cb .. cb + nc - 1 of the right-hand sides [ w | [z; 0] | [0; I_l] ]
     zero_x();
     wave_lds_sync();
-    if constexpr (MODE == 7) {
-      for (int j = ln; j < m; j += 64) X[j * LDX] = sw[j];
-    } else {
-      for (int c = ln; c < nc; c += 64)
-        if (cb + c >= 2) X[(m + cb + c - 2) * LDX + c] = T(1);
-      if (cb == 0) {
-        for (int j = ln; j < p; j += 64) {
-          X[j * LDX] = sw[j];
-          if (j < m) X[j * LDX + 1] = sw[j];
-        }
+    for (int c = ln; c < nc; c += 64)
+      if (cb + c >= 2) X[(m + cb + c - 2) * LDX + c] = T(1);
+    if (cb == 0) {
+      for (int j = ln; j < p; j += 64) {
+        X[j * LDX] = sw[j];
+        if (j < m) X[j * LDX + 1] = sw[j];
       }
     }
     wave_lds_sync();
@@ -1135,11 +1121,6 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
       });
       wave_lds_sync();
     });
-    if constexpr (MODE == 7) {
-      for (int j = ln; j < m; j += 64) a.coef[(size_t)tt * a.coef_stride + n0 + j] = X[j * LDX];
-      if (ln == 0) a.cvar[o] = var;
-      return;
-    }
     contract(cb, nc);
     if constexpr (!wave_regadj_passes(G, sizeof(T) == 4)) break;   // one pass: nr <= CH
     }
@@ -1348,23 +1329,6 @@ static hipError_t launch_wave_t(int g, const AdjArgs& a, const ThetaPack& thp, i
 #endif
       default: return hipErrorInvalidValue;
     }
-  } else if constexpr (MODE == 7) {   // simulator: FP64 only
-    if constexpr (sizeof(T) == 8) {
-      switch (g) {
-        case 1: return launch_wave_g<T, 1, MODE, GEN>(a, thp, grid, s);
-        case 2: return launch_wave_g<T, 2, MODE, GEN>(a, thp, grid, s);
-        case 3: return launch_wave_g<T, 3, MODE, GEN>(a, thp, grid, s);
-        case 4: return launch_wave_g<T, 4, MODE, GEN>(a, thp, grid, s);
-        case 5: return launch_wave_g<T, 5, MODE, GEN>(a, thp, grid, s);
-        case 6: return launch_wave_g<T, 6, MODE, GEN>(a, thp, grid, s);
-        case 7: return launch_wave_g<T, 7, MODE, GEN>(a, thp, grid, s);
-        case 8: return launch_wave_g<T, 8, MODE, GEN>(a, thp, grid, s);
-        case 9: return launch_wave_g<T, 9, MODE, GEN>(a, thp, grid, s);
-        case 10: return launch_wave_g<T, 10, MODE, GEN>(a, thp, grid, s);
-        default: break;
-      }
-    }
-    return hipErrorInvalidValue;
   } else if constexpr (MODE == 6) {   // left-looking factorisation: FP64 above G = 9
     if constexpr (sizeof(T) == 8) {
       if (g == 10) return launch_wave_g<T, 10, MODE, GEN>(a, thp, grid, s);
@@ -1400,6 +1364,17 @@ static hipError_t launch_wave_t(int g, const AdjArgs& a, const ThetaPack& thp, i
       case 7: return launch_wave_g<T, 7, MODE, GEN>(a, thp, grid, s);
       case 8: return launch_wave_g<T, 8, MODE, GEN>(a, thp, grid, s);
       case 9: return launch_wave_g<T, 9, MODE, GEN>(a, thp, grid, s);
+      default: return hipErrorInvalidValue;
+    }
+  } else if constexpr (MODE == 0 && sizeof(T) == 8 && !GEN) {   // (G = 7 .. 10: wave_rows.hpp)
+    switch (g) {
+      case 1: return launch_wave_g<T, 1, MODE, GEN>(a, thp, grid, s);
+      case 2: return launch_wave_g<T, 2, MODE, GEN>(a, thp, grid, s);
+      case 3: return launch_wave_g<T, 3, MODE, GEN>(a, thp, grid, s);
+      case 4: return launch_wave_g<T, 4, MODE, GEN>(a, thp, grid, s);
+      case 5: return launch_wave_g<T, 5, MODE, GEN>(a, thp, grid, s);
+      case 6: return launch_wave_g<T, 6, MODE, GEN>(a, thp, grid, s);
+      case 11: return launch_wave_g<T, 11, MODE, GEN>(a, thp, grid, s);
       default: return hipErrorInvalidValue;
     }
   } else {
