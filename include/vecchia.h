@@ -64,9 +64,9 @@ typedef enum {
  *   h = || (s_i - s_j) / aniso ||  (componentwise division; aniso = {1,1,1}
  *   is isotropic).  nu = 0.5, 1.5, 2.5 use the closed forms rho = e^-x,
  *   (1+x) e^-x, (1 + x + x^2/3) e^-x; any other nu in [0.05, 10] uses
- *   rho = 2^(1-nu)/Gamma(nu) x^nu K_nu(x), evaluated in FP64 (Temme's series
- *   for x <= 2, the trapezoidal rule on the integral representation of K for
- *   x > 2, upward recurrence in the order) by the one-wave kernels
+ *   rho = 2^(1-nu)/Gamma(nu) x^nu K_nu(x), evaluated in FP64 (the
+ *   trapezoidal rule on the integral representation of K, Temme's series for
+ *   x < 6e-8, upward recurrence in the order) by the one-wave kernels
  *   only: other engines, blocks above VECCHIA_MAX_JOINT and the simulator
  *   return VECCHIA_EUNSUPPORTED for it, as for nu outside [0.05, 10].  The
  *   nugget applies to same-index pairs only (not to distinct points at

@@ -27,7 +27,8 @@ namespace bv {
 // waits in LDS, and its updates are applied to every other tile as that is generated.
 template <int G> constexpr int rows_deferred() { return G >= 10 ? 1 : 0; }
 template <int G, bool COEF> constexpr int rows_min_waves() {
-  return G <= 2 ? 4 : G <= 3 ? 3 : G <= 5 ? 2 : 1;   // the most without scratch (weights; the value has G >= 7 only)
+  // the most that leave the weights without scratch (G = 5: 100 bytes); the value has G >= 7 only
+  return G <= 2 ? 4 : G <= 3 ? 3 : G <= 5 ? 2 : 1;
 }
 // LDS elements: coordinates, y, pivots, border row, the published columns, the first
 // tile column, and for the weights the 4 x 4 inverses and one tile
