@@ -389,6 +389,8 @@ extern "C" int vecchia_plan_class_kernel(const vecchia_plan* plan, int32_t q, in
                           : snprintf(name, (size_t)cap, "bv_large_f64_kernel");
   else if (mode == 23 || mode == 63)
     n = snprintf(name, (size_t)cap, "bv_wave_kernel<%s,%d,%d>+bv_wave_kernel<%s,%d,3>", t, g, mode / 10, t, g);
+  else if (mode == 0 && !fp32 && g >= 7 && g <= 10)   // closed forms (wave_rows.hpp)
+    n = snprintf(name, (size_t)cap, "bv_rows_kernel<%d,false>", g);
   else if (mode >= 0)
     n = snprintf(name, (size_t)cap, "bv_wave_kernel<%s,%d,%d>", t, g, mode);
   else if (plan->engine == kEngineTiles)

@@ -239,26 +239,72 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   if (MODE == 4 && l == 0) return;
   const double* org = (MODE == 4 ? a.locs2 : a.locs) + (size_t)b0 * a.d;   // coordinate origin: the block's first point
 
-  for (int i = ln; i < P; i += 64) {
-    if (real_row(i)) {
-      const double* src;
-      if (MODE == 4) {
-        const bool nb = i < m;
-        src = nb ? a.locs + (size_t)a.nbr_idx[n0 + i] * a.d : a.locs2 + (size_t)(b0 + i - mq) * a.d;
-        sy[i] = nb ? T(a.y[a.nbr_idx[n0 + i]]) : T(0);   // the border row is [y_N, 0]
+  // All rows' indices are read before any of their points, and all points before
+  // any is stored (rows that hold none read the block's first point or the last
+  // neighbour): the wave waits for two loads in turn whatever its rows, not two
+  // per 64 rows (FP32 value and gradient at n = 1e6 3.10 -> 3.02 ms, prediction at
+  // n = 1e5 770 -> 751 us).  With three and more waves per SIMD the others cover
+  // it, and 64 rows at a time need fewer registers; mode 6 has none to spare either
+  // (left to itself the loop costs it scratch at G = 10, rolled at G = 11).
+  constexpr int NR = wave_min_waves<T, G, MODE, GEN>() <= 2 && MODE != 6 ? (P + 63) / 64 : 1;
+  constexpr int ROLL = MODE == 6 && G == 10 ? 1 : (P + 63) / 64;
+#pragma unroll ROLL
+  for (int row0 = 0; row0 < P; row0 += 64 * NR) {
+    int gi[NR];
+    T yv[NR];
+    double x[NR][3];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      gi[q] = 0;
+      yv[q] = T(0);
+    }
+    if (m > 0) {
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        const int i = row0 + ln + 64 * q;
+        gi[q] = a.nbr_idx[n0 + (i < m ? i : m - 1)];
+      }
+    }
+    if (MODE == 4 && m > 0) {   // the border row is [y_N, 0]
+#pragma unroll
+      for (int q = 0; q < NR; ++q) yv[q] = T(a.y[gi[q]]);
+    }
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const int i = row0 + ln + 64 * q;
+      if (i >= m) gi[q] = i >= mq && i < p ? b0 + i - mq : b0;
+    }
+    if (MODE != 3 && MODE != 4) {
+#pragma unroll
+      for (int q = 0; q < NR; ++q) yv[q] = T(a.y[gi[q]]);
+    }
+    double og[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      og[k] = 0.0;
+      if (k < a.d) {
+        og[k] = org[k];
+#pragma unroll
+        for (int q = 0; q < NR; ++q)
+          x[q][k] = (MODE == 4 && row0 + ln + 64 * q >= m ? a.locs2 : a.locs)[(size_t)gi[q] * a.d + k];
       } else {
-        const int g = (i < m) ? a.nbr_idx[n0 + i] : (b0 + i - m);
-        src = a.locs + (size_t)g * a.d;
-        if (MODE != 3) sy[i] = T(a.y[g]);
+#pragma unroll
+        for (int q = 0; q < NR; ++q) x[q][k] = 0.0;
       }
-      for (int k = 0; k < 3; ++k) {
-        T v = k < a.d ? T((src[k] - org[k]) * (th.inv_scale[k] * UNIT)) : T(0);
-        if constexpr (sizeof(T) == 8) v = v > 1e140 ? 1e140 : v < -1e140 ? -1e140 : v;   // squares stay finite
-        su[k * P + i] = v;
+    }
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const int i = row0 + ln + 64 * q;
+      if (i < P) {
+        const bool real = real_row(i);
+        if (MODE != 3) sy[i] = real && (MODE != 4 || i < m) ? yv[q] : T(0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          T v = k < a.d ? T((x[q][k] - og[k]) * (th.inv_scale[k] * UNIT)) : T(0);
+          if constexpr (sizeof(T) == 8) v = v > 1e140 ? 1e140 : v < -1e140 ? -1e140 : v;   // squares stay finite
+          su[k * P + i] = real ? v : T(0);
+        }
       }
-    } else {
-      if (MODE != 3) sy[i] = T(0);
-      for (int k = 0; k < 3; ++k) su[k * P + i] = T(0);
     }
   }
   wave_lds_sync();

@@ -10,13 +10,14 @@
 // untransposed, as its contraction of the gradient wants them, and writes and reads
 // the whole panel through LDS.
 //
-// What bounds it: the FP64 units, which the matrix and vector instructions share.
-// G = 9: 795 products of 64 cycles, 45 tiles generated in about 900 cycles each and
-// 36 dependent chains (one per panel) of about 700: 116,000 cycles a wave of the
-// measured 172,000; the rest is fetching 150 KB of straight-line code.
-// n = 1e6, m = 120 (G = 9), value: 3.74 ms with the general kernel, 3.49 now.
-// Simulator, 24 sets of n = 20,000, m = 150 (G = 10): 80.4 ms with the general kernel (its
-// tiles beyond the registers in scratch), 58.6 now.
+// What bounds it: one wave per SIMD from G = 6 or 7 on, so every wait shows.  G = 9: a
+// wave lives 154,000 cycles, of which 795 matrix products take 51,000, other vector
+// instructions about as much, and waits (LDS, the gathers, results of the
+// products and of the pivots' chains) the rest; instruction fetch is no matter
+// (150 KB of code, 0.2 % misses).
+// n = 1e6, m = 120 (G = 9), value: 3.74 ms with the general kernel, 3.42 now.
+// Simulator, 24 sets of n = 20,000, m = 150 (G = 10): 80.4 ms with the general
+// kernel, 58.1 now (both with part of the tiles in scratch).
 #pragma once
 #include "wave_kernel.hpp"
 
@@ -85,19 +86,46 @@ __global__ void __launch_bounds__(64, (rows_min_waves<G, COEF>())) bv_rows_kerne
   const int l = b1 - b0, m = n1 - n0, p = m + l;
   const int brow = COEF ? m : p;   // the row whose factor entries are kept: y_J, or the point's own
   const double* org = a.locs + (size_t)b0 * a.d;
-  for (int i = ln; i < P; i += 64) {
-    double v[3] = {0.0, 0.0, 0.0}, yv = 0.0;
-    if (i < p) {
-      const int g = i < m ? a.nbr_idx[n0 + i] : b0 + i - m;
-      if (!COEF) yv = a.y[g];
-      for (int k = 0; k < a.d; ++k) {
-        const double x = (a.locs[(size_t)g * a.d + k] - org[k]) * (th.inv_scale[k] * kLog2E);
-        v[k] = x > 1e140 ? 1e140 : x < -1e140 ? -1e140 : x;   // squares stay finite
+  {
+    // all rows' indices before their points, all points before the first store (as
+    // in the general kernel; rows past p read the block's first point)
+    constexpr int NR = (P + 63) / 64;
+    int gi[NR];
+    double yv[NR], x[NR][3], og[3];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) gi[q] = 0;
+    if (m > 0) {
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        const int i = ln + 64 * q;
+        gi[q] = a.nbr_idx[n0 + (i < m ? i : m - 1)];
       }
     }
-    sy[i] = yv;
 #pragma unroll
-    for (int k = 0; k < 3; ++k) su[k * P + i] = v[k];
+    for (int q = 0; q < NR; ++q) {
+      const int i = ln + 64 * q;
+      if (i >= m) gi[q] = i < p ? b0 + i - m : b0;
+      yv[q] = COEF ? 0.0 : a.y[gi[q]];
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      og[k] = k < a.d ? org[k] : 0.0;
+#pragma unroll
+      for (int q = 0; q < NR; ++q) x[q][k] = k < a.d ? a.locs[(size_t)gi[q] * a.d + k] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      const int i = ln + 64 * q;
+      if (i < P) {
+        sy[i] = i < p ? yv[q] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          double v = k < a.d ? (x[q][k] - og[k]) * (th.inv_scale[k] * kLog2E) : 0.0;
+          v = v > 1e140 ? 1e140 : v < -1e140 ? -1e140 : v;   // squares stay finite
+          su[k * P + i] = i < p ? v : 0.0;
+        }
+      }
+    }
   }
   wave_lds_sync();
   const MaternCoef<double> mc(th.nu_code);
