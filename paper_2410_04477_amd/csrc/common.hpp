@@ -109,8 +109,9 @@ __device__ inline void bessel_k_pair_quad(double x, double mu, double& k_mu, dou
 // three-term recurrence K_(v+1) = K_(v-1) + (2 v / x) K_v, which is stable
 // upwards for K.  Also returns g = 2^(1-nu)/Gamma(nu) x^(nu+1) K_(nu-1)(x),
 // from d/dx [x^nu K_nu(x)] = -x^nu K_(nu-1)(x): d rho(h/range) / d range =
-// g / range.  Not inlined: the kernels call it only for distances outside the
-// range of bessel4 below.
+// g / range.  Not inlined: its loops would otherwise be copied into every
+// generation site.  The FP64 kernels call it only for distances outside the range of
+// bessel4 below, the FP32 kernels for all.
 __device__ __noinline__ inline void matern_general(double x, const BesselOrder& o, double* rho, double* g) {
   if (!(x > 1e-140)) {   // a coincident pair (distance<double> gives 1e-150)
     *rho = 1.0;

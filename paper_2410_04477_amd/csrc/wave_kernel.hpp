@@ -316,10 +316,13 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   double acc_ll = 0.0;
   int flag = 0;
   const MaternCoef<T> mc(th.nu_code);   // closed forms
-  // Bessel form: the table of this order, after the rest of the LDS
+  // Bessel form, FP64: the table of this order, after the rest of the LDS.  (FP32
+  // rounds the FP64 function; it keeps the function by single distances, whose last
+  // bits differ, as a changed rounding of one covariance moves the FP32 results.)
+  constexpr bool BES4 = GEN && sizeof(T) == 8;
   double* const table = reinterpret_cast<double*>(smem + wave_table_offset(sizeof(T), G, MODE));
   LdsDouble* const btab = (LdsDouble*)table;
-  if constexpr (GEN) {
+  if constexpr (BES4) {
     bessel_table(table, th.bes, ln);
     wave_lds_sync();
   }
@@ -361,6 +364,13 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
     BesselOut bes;
     if constexpr (!GEN) {
       distance_exp2neg4<STAGED>(dx, dy, dz, u, e);
+    } else if constexpr (!BES4) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        double rho, g;
+        matern_general((double)distance<T>(dx[r], dy[r], dz[r]), th.bes, &rho, &g);
+        bes[r] = rho;
+      }
     } else {
       Bessel4 x;
 #pragma unroll
@@ -990,6 +1000,18 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   // d l / d sigma2 = (sum_{k >= m} w_k^2 - l - nugget tr W) / (2 sigma2)
   double g1 = 0.0, g2 = 0.0, qb = 0.0, g3 = 0.0;   // g3: <W, d rho / d nu> (Bessel form, on request)
   const bool want_nu = GEN && a.gnu != nullptr;
+  // FP32 Bessel form: one distance at a time
+  auto drange = [&](T x) __attribute__((always_inline)) {
+    double rho, g;
+    matern_general((double)x, th.bes, &rho, &g);
+    return T(g) * irange;
+  };
+  auto drange_dnu = [&](T x, T& dr, T& dn) __attribute__((always_inline)) {
+    double rho, g, v;
+    matern_general_dnu((double)x, th.bes, &rho, &g, &v);
+    dr = T(g) * irange;
+    dn = T(v);
+  };
   // W = alpha alpha^T - b b^T - X_R X_R^T over the right-hand sides [cb, cb + nc)
   // held in X, contracted with dK regenerated entry by entry
   auto contract = [&](int cb, int nc) __attribute__((always_inline)) {
@@ -1050,16 +1072,26 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
         BesselOut bes;   // g of the four, then their d rho / d nu
         if constexpr (!GEN) {
           distance_exp2neg4<STAGED>(dx, dy, dz, u, e);
-        } else {
+        } else if constexpr (BES4) {
           Bessel4 x;
 #pragma unroll
           for (int r = 0; r < 4; ++r) x[r] = (double)distance<T>(dx[r], dy[r], dz[r]);
           bes = want_nu ? bessel4<2>(x, btab) : bessel4<1>(x, btab);
         }
         auto entry = [&](int r) __attribute__((always_inline)) {
-          if constexpr (GEN) {
+          if constexpr (BES4) {
             s1 += c[r] * (T(bes[r]) * irange);
             if (want_nu) s3 += c[r] * T(bes[r + 4]);
+          } else if constexpr (GEN) {
+            const T x = distance<T>(dx[r], dy[r], dz[r]);
+            if (want_nu) {
+              T dr, dn;
+              drange_dnu(x, dr, dn);
+              s1 += c[r] * dr;
+              s3 += c[r] * dn;
+            } else {
+              s1 += c[r] * drange(x);
+            }
           } else {
             s1 += c[r] * mc.drange_log2(u[r], e[r], dh0, dh1, dh2);
           }
@@ -1349,8 +1381,8 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
 
 template <typename T, int G, int MODE, bool GEN>
 static hipError_t launch_wave_g(const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s) {
-  const size_t lds = GEN ? (size_t)wave_table_offset(sizeof(T), G, MODE) + kBesselBytes
-                         : sizeof(T) * (size_t)wave_lds_elems(G, MODE);
+  const size_t lds = GEN && sizeof(T) == 8 ? (size_t)wave_table_offset(sizeof(T), G, MODE) + kBesselBytes
+                                           : sizeof(T) * (size_t)wave_lds_elems(G, MODE);
   hipLaunchKernelGGL((bv_wave_kernel<T, G, MODE, GEN>), dim3(grid), dim3(64), lds, s, a, thp);
   return hipGetLastError();
 }
