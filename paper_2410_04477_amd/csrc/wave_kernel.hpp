@@ -115,16 +115,20 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// elements of the panel: four columns of P rows; in the modes that form the diagonal
+// inverses during the factorisation also 16 appended rows, and the panel is the
+// scratch of a 16 x 16 transposition too (which exceeds four columns up to G = 2)
+__host__ __device__ constexpr int wave_panel(int G, bool einv) {
+  return einv ? wave_max(4 * (16 * G + 16), 256) : 4 * 16 * G;
+}
 __host__ __device__ constexpr int wave_lds_elems(int G, int mode) {
-  // su (3 P) for the whole kernel, then a work region: the panel (4 columns of
-  // P rows, plus 16 appended rows in the modes that form the diagonal inverses
-  // during the factorisation) and sy, sdk, swk (P each) during the
-  // factorisation; for the adjoint, one chunk of right-hand sides
+  // su (3 P) for the whole kernel, then a work region: the panel and sy, sdk, swk
+  // (P each) during the factorisation; for the adjoint, one chunk of right-hand sides
   // (P x (wave_chunk(G) + 1), plus 32 elements that reads of the last row's
   // unused columns may touch), which also holds the G staged diagonal tiles
   // before the first chunk
   // (mode 5 keeps the border row w of the factor after that, 16 G elements)
-  return 3 * 16 * G + wave_max(4 * (16 * G + (mode == 2 || mode == 5 || mode == 6 ? 16 : 0)) + 3 * 16 * G,
+  return 3 * 16 * G + wave_max(wave_panel(G, mode == 2 || mode == 5 || mode == 6) + 3 * 16 * G,
                                mode == 0 || mode == 2 || mode == 4 || mode == 6 ? 0
                                : (16 * (wave_chunk(G) + 1) > kStageStride
                                       ? 16 * G * (wave_chunk(G) + 1) + 32
@@ -202,10 +206,7 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   constexpr bool INREG = MODE == 5;                // factor kept in the registers
   constexpr bool EINV = INREG || MODE == 2 || LEFT;   // diagonal inverses formed during the factorisation
   constexpr int PS = EINV ? P + 16 : P;            // panel column stride
-  // the panel, also the scratch of the 16 x 16 transposition, which the panel of
-  // G <= 2 does not hold (KNOWN FAULT, left as it was: in modes 2, 5 and 6 it then
-  // overwrites the pivots, and the value and gradient of classes G <= 2 come out NaN)
-  constexpr int PANEL = 4 * PS;
+  constexpr int PANEL = wave_panel(G, EINV);
   static_assert(3 * P + PANEL + 3 * P <= wave_lds_elems(G, MODE), "factorisation LDS");
   T* sy = work + PANEL;                // border row y_J
   T* sdk = sy + P;                     // pivots d_k
