@@ -213,15 +213,20 @@ template <> __device__ __forceinline__ double expneg<double>(double x) { return 
 template <> __device__ __forceinline__ float expneg<float>(float x) { return __expf(-x); }
 
 // 2^-x.  FP32: one v_exp_f32.  FP64, x >= 0: 2^-x = 2^m 2^f with m = -x rounded
-// to an integer and f = -x - m exact, |f| <= 1/2, and 2^f = 1 + f q(f), q the
+// to an integer (by adding 3 2^51: the sum's low word is m, with no conversion, which
+// would be undefined beyond 32 bits; hence the bound, past which 2^-x is zero)
+// and f = -x - m exact, |f| <= 1/2, and 2^f = 1 + f q(f), q the
 // degree-10 interpolant of (2^f - 1) / f at the Chebyshev nodes (8.4e-18
 // relative; with rounding 1.35e-16 at most and 3.8e-17 in the mean over
-// x in [1e-10, 1e3], as the library's exp2): 16 instructions.  A NaN or infinite
-// x gives NaN.
+// x in [1e-10, 1e3], as the library's exp2): 16 instructions.  A NaN x gives zero: the
+// callers multiply by a polynomial in x.
+constexpr double kExpBound = 1100.0, kExpShift = 0x1.8p52;
+__device__ __forceinline__ int low_word(double t) { return (int)__builtin_bit_cast(unsigned long long, t); }
 template <typename T> __device__ __forceinline__ T exp2neg(T x);
 template <> __device__ __forceinline__ double exp2neg<double>(double x) {
-  const double m = __builtin_rint(-x);
-  const double f = -x - m;
+  x = __builtin_fmin(x, kExpBound);
+  const double t = kExpShift - x;
+  const double f = -x - (t - kExpShift);
   double q = 0x1.e9d3fe3952179p-32;
   q = __builtin_fma(q, f, 0x1.e6063f7217bc6p-28);
   q = __builtin_fma(q, f, 0x1.b524fae627834p-24);
@@ -234,7 +239,7 @@ template <> __device__ __forceinline__ double exp2neg<double>(double x) {
   q = __builtin_fma(q, f, 0x1.ebfbdff82c598p-3);
   q = __builtin_fma(q, f, 0x1.62e42fefa39efp-1);
   q = __builtin_fma(q, f, 1.0);
-  return __builtin_amdgcn_ldexp(q, (int)m);
+  return __builtin_amdgcn_ldexp(q, low_word(t));
 }
 template <> __device__ __forceinline__ float exp2neg<float>(float x) { return __builtin_amdgcn_exp2f(-x); }
 
@@ -328,7 +333,7 @@ __device__ __forceinline__ void distance_exp2neg4(const double (&dx)[4], const d
     _Pragma("unroll") for (int r = 0; r < 4; ++r) { __VA_ARGS__; } \
     __builtin_amdgcn_sched_barrier(0);           \
   } while (0)
-  double y[4], e[4], t[4], m[4];
+  double y[4], e[4], t[4];
   BV_STEP(u[r] = __builtin_fma(dz[r], dz[r], 1e-300));
   BV_STEP(u[r] = __builtin_fma(dy[r], dy[r], u[r]));
   BV_STEP(u[r] = __builtin_fma(dx[r], dx[r], u[r]));
@@ -338,8 +343,11 @@ __device__ __forceinline__ void distance_exp2neg4(const double (&dx)[4], const d
   BV_STEP(t[r] = __builtin_fma(e[r], 0.375, 0.5));
   BV_STEP(e[r] = u[r] * e[r]);
   BV_STEP(u[r] = __builtin_fma(e[r], t[r], u[r]));
-  BV_STEP(m[r] = __builtin_rint(-u[r]));
-  BV_STEP(y[r] = -u[r] - m[r]);
+  int m[4];
+  BV_STEP(e[r] = __builtin_fmin(u[r], kExpBound));
+  BV_STEP(t[r] = kExpShift - e[r]);
+  BV_STEP(y[r] = t[r] - kExpShift; m[r] = low_word(t[r]));
+  BV_STEP(y[r] = -e[r] - y[r]);
   BV_STEP(w[r] = __builtin_fma(0x1.e9d3fe3952179p-32, y[r], 0x1.e6063f7217bc6p-28));
   BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.b524fae627834p-24));
   BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.62bfd47773353p-20));
@@ -351,7 +359,7 @@ __device__ __forceinline__ void distance_exp2neg4(const double (&dx)[4], const d
   BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.ebfbdff82c598p-3));
   BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.62e42fefa39efp-1));
   BV_STEP(w[r] = __builtin_fma(w[r], y[r], 1.0));
-  BV_STEP(w[r] = __builtin_amdgcn_ldexp(w[r], (int)m[r]));
+  BV_STEP(w[r] = __builtin_amdgcn_ldexp(w[r], m[r]));
 #undef BV_STEP
 }
 template <bool STAGED>
