@@ -309,7 +309,8 @@ int vecchia_plan_timing(vecchia_plan* plan, double* ms, int64_t* launches, int r
  *   loglik       out, ntheta doubles
  *   counters     out or NULL, 2*ntheta int32: [t*2+0] blocks re-factorised in
  *                FP64 by the FP32 guard, [t*2+1] blocks that were not positive
- *                definite even in FP64 (then loglik[t] is NaN)
+ *                definite even in FP64 (then loglik[t] is NaN); a block with a
+ *                coordinate that is not finite is one of them
  *   partial      out or NULL, ntheta*bc doubles: per-block terms l_i,
  *                [t*bc + i]
  * The FP32 guard flags a block when a pivot d_k (the diagonal before the

@@ -103,10 +103,7 @@ __global__ void __launch_bounds__(256, 2) bv_large_f64_kernel(LargeArgs a, Theta
       const int gi = i < m ? a.nbr_idx[n0 + i] : (b0 + i - m);
       for (int k = 0; k < 3; ++k) {
         double v = 0.0;
-        if (i < p && k < d) {
-          v = (a.locs[(size_t)gi * d + k] - a.locs[(size_t)b0 * d + k]) * (th.inv_scale[k] * kLog2E);
-          v = v > 1e140 ? 1e140 : v < -1e140 ? -1e140 : v;   // squares stay finite
-        }
+        if (i < p && k < d) v = (a.locs[(size_t)gi * d + k] - a.locs[(size_t)b0 * d + k]) * (th.inv_scale[k] * kLog2E);
         cs[k * ld + i] = v;
       }
     }

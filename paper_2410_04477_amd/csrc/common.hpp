@@ -113,7 +113,7 @@ __device__ inline void bessel_k_pair_quad(double x, double mu, double& k_mu, dou
 // generation site.  The FP64 kernels call it only for distances outside the range of
 // bessel4 below, the FP32 kernels for all.
 __device__ __noinline__ inline void matern_general(double x, const BesselOrder& o, double* rho, double* g) {
-  if (!(x > 1e-140)) {   // a coincident pair (distance<double> gives 1e-150)
+  if (x <= 1e-140) {   // a coincident pair (distance<double> gives 1e-150); a NaN goes on to NaN
     *rho = 1.0;
     *g = 0.0;
     return;
@@ -152,7 +152,7 @@ __device__ __noinline__ inline void matern_general(double x, const BesselOrder& 
 // psi(nu)) + D_nu].
 __device__ __noinline__ inline void matern_general_dnu(double x, const BesselOrder& o, double* rho, double* g,
                                                        double* drho_dnu) {
-  if (!(x > 1e-140)) {   // a coincident pair (distance<double> gives 1e-150)
+  if (x <= 1e-140) {   // a coincident pair (distance<double> gives 1e-150); a NaN goes on to NaN
     *rho = 1.0;
     *g = 0.0;
     *drho_dnu = 0.0;
@@ -300,7 +300,8 @@ __device__ __forceinline__ double rsqrt_fast(double x) {
 
 // Distance sqrt(dx^2 + dy^2 + dz^2).  FP64: from the estimate of 1 / sqrt in one
 // third-order step as above; the sum starts from 1e-300, so coincident points
-// come out at 1e-150 instead of 0 * inf.
+// come out at 1e-150 instead of 0 * inf.  A sum of squares that overflows, and any
+// coordinate that is not finite, gives NaN, and so does the covariance.
 template <typename T> __device__ __forceinline__ T distance(T dx, T dy, T dz);
 template <> __device__ __forceinline__ double distance<double>(double dx, double dy, double dz) {
   const double x = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, 1e-300)));
@@ -493,10 +494,11 @@ __device__ __noinline__ inline BesselOut bessel4(Bessel4 x, LdsDouble* tab) {
     }
     const double logx = log(z);
     const double c = w * exp(lognorm + nu * logx);
-    const bool at0 = !(x[r] > 1e-140);   // a coincident pair (distance<double> gives 1e-150)
-    if (WHAT == 0) out[r] = at0 ? 1.0 : c * khi;
-    if (WHAT >= 1) out[r] = at0 ? 0.0 : c * z * klo;
-    if (DNU) out[r + 4] = at0 ? 0.0 : c * (khi * (logx + dlognorm) + dhi);
+    const bool at0 = x[r] <= 1e-140;   // a coincident pair (distance<double> gives 1e-150)
+    const double nan = x[r] - x[r];    // 0, or NaN for the distance of a point that is not finite
+    if (WHAT == 0) out[r] = at0 ? 1.0 : c * khi + nan;
+    if (WHAT >= 1) out[r] = at0 ? 0.0 : c * z * klo + nan;
+    if (DNU) out[r + 4] = at0 ? 0.0 : c * (khi * (logx + dlognorm) + dhi) + nan;
   }
   if (__any(rare)) {
     BesselOrder o;

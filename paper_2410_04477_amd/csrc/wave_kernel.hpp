@@ -300,11 +300,8 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
         const bool real = real_row(i);
         if (MODE != 3) sy[i] = real && (MODE != 4 || i < m) ? yv[q] : T(0);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          T v = k < a.d ? T((x[q][k] - og[k]) * (th.inv_scale[k] * UNIT)) : T(0);
-          if constexpr (sizeof(T) == 8) v = v > 1e140 ? 1e140 : v < -1e140 ? -1e140 : v;   // squares stay finite
-          su[k * P + i] = real ? v : T(0);
-        }
+        for (int k = 0; k < 3; ++k)
+          su[k * P + i] = real && k < a.d ? T((x[q][k] - og[k]) * (th.inv_scale[k] * UNIT)) : T(0);
       }
     }
   }

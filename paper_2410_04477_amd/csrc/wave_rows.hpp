@@ -119,11 +119,8 @@ __global__ void __launch_bounds__(64, (rows_min_waves<G, COEF>())) bv_rows_kerne
       if (i < P) {
         sy[i] = i < p ? yv[q] : 0.0;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          double v = k < a.d ? (x[q][k] - og[k]) * (th.inv_scale[k] * kLog2E) : 0.0;
-          v = v > 1e140 ? 1e140 : v < -1e140 ? -1e140 : v;   // squares stay finite
-          su[k * P + i] = i < p ? v : 0.0;
-        }
+        for (int k = 0; k < 3; ++k)
+          su[k * P + i] = i < p && k < a.d ? (x[q][k] - og[k]) * (th.inv_scale[k] * kLog2E) : 0.0;
       }
     }
   }
