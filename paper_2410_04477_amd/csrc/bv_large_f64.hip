@@ -115,7 +115,8 @@ __global__ void __launch_bounds__(256, 2) bv_large_f64_kernel(LargeArgs a, Theta
     };
     // -C_IJ^T before the updates; column tile c of the panel
     auto generate = [&](int I, int J, int c) __attribute__((always_inline)) {
-      double dx[4], dy[4], dz[4], u[4], e[4];
+      double dx[4], dy[4], dz[4], u[4];
+      Exp2Parts e[4];
       d4_t v;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {

@@ -220,10 +220,17 @@ template <> __device__ __forceinline__ float expneg<float>(float x) { return __e
 // relative; with rounding 1.35e-16 at most and 3.8e-17 in the mean over
 // x in [1e-10, 1e3], as the library's exp2): 16 instructions.  A NaN x gives zero: the
 // callers multiply by a polynomial in x.
-constexpr double kExpBound = 1100.0, kExpShift = 0x1.8p52;
+constexpr double kExpBound = 2200.0, kExpShift = 0x1.8p52;
 __device__ __forceinline__ int low_word(double t) { return (int)__builtin_bit_cast(unsigned long long, t); }
-template <typename T> __device__ __forceinline__ T exp2neg(T x);
-template <> __device__ __forceinline__ double exp2neg<double>(double x) {
+// 2^-x as 2^m (1 + w): the products with it round once (scaled)
+struct Exp2Parts {
+  double w;
+  int m;
+};
+__device__ __forceinline__ double scaled(const Exp2Parts& e, double p) {
+  return __builtin_amdgcn_ldexp(__builtin_fma(e.w, p, p), e.m);
+}
+__device__ __forceinline__ Exp2Parts exp2neg_parts(double x) {
   x = __builtin_fmin(x, kExpBound);
   const double t = kExpShift - x;
   const double f = -x - (t - kExpShift);
@@ -238,9 +245,10 @@ template <> __device__ __forceinline__ double exp2neg<double>(double x) {
   q = __builtin_fma(q, f, 0x1.c6b08d704a0c2p-5);
   q = __builtin_fma(q, f, 0x1.ebfbdff82c598p-3);
   q = __builtin_fma(q, f, 0x1.62e42fefa39efp-1);
-  q = __builtin_fma(q, f, 1.0);
-  return __builtin_amdgcn_ldexp(q, low_word(t));
+  return {q * f, low_word(t)};
 }
+template <typename T> __device__ __forceinline__ T exp2neg(T x);
+template <> __device__ __forceinline__ double exp2neg<double>(double x) { return scaled(exp2neg_parts(x), 1.0); }
 template <> __device__ __forceinline__ float exp2neg<float>(float x) { return __builtin_amdgcn_exp2f(-x); }
 
 template <typename T> __device__ __forceinline__ T sqrt_(T x);
@@ -279,12 +287,20 @@ struct MaternCoef {
     return x * inv_range * expneg<T>(x) * (g0 + x * (g1 + g2 * x));
   }
   // -(sigma2 rho) and d rho / d range for a distance u = x log2(e) and e = 2^-u = e^-x
-  // with the scales and sign in the coefficients: (s0, s1, s2) =
+  // (FP64: its parts) with the scales and sign in the coefficients: (s0, s1, s2) =
   // -sigma2 (1, c1 ln 2, c2 ln(2)^2), (h0, h1, h2) = (g0 ln 2, g1 ln(2)^2,
   // g2 ln(2)^3) / range
-  static __device__ __forceinline__ T neg_cov_log2(T u, T e, T s0, T s1, T s2) { return e * (s0 + u * (s1 + s2 * u)); }
-  static __device__ __forceinline__ T drange_log2(T u, T e, T h0, T h1, T h2) {
+  static __device__ __forceinline__ float neg_cov_log2(float u, float e, float s0, float s1, float s2) {
+    return e * (s0 + u * (s1 + s2 * u));
+  }
+  static __device__ __forceinline__ float drange_log2(float u, float e, float h0, float h1, float h2) {
     return u * e * (h0 + u * (h1 + h2 * u));
+  }
+  static __device__ __forceinline__ double neg_cov_log2(double u, const Exp2Parts& e, double s0, double s1, double s2) {
+    return scaled(e, s0 + u * (s1 + s2 * u));
+  }
+  static __device__ __forceinline__ double drange_log2(double u, const Exp2Parts& e, double h0, double h1, double h2) {
+    return scaled(e, u * (h0 + u * (h1 + h2 * u)));
   }
 };
 
@@ -298,21 +314,29 @@ __device__ __forceinline__ double rsqrt_fast(double x) {
   return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
 }
 
-// Distance sqrt(dx^2 + dy^2 + dz^2).  FP64: from the estimate of 1 / sqrt in one
-// third-order step as above; the sum starts from 1e-300, so coincident points
+// Distance sqrt(dx^2 + dy^2 + dz^2).  FP64: from the estimate y of 1 / sqrt, g = x y
+// with one second-order step (2^-47) and one with the exact residual x - g^2, which
+// leaves the rounding of the last operation (1.1e-16, as the library's square
+// root; a third-order step instead of the two is one operation less and 1.4e-16).
+// The sum starts from 1e-300, so coincident points
 // come out at 1e-150 instead of 0 * inf.  A sum of squares that overflows, and any
 // coordinate that is not finite, gives NaN, and so does the covariance.
 template <typename T> __device__ __forceinline__ T distance(T dx, T dy, T dz);
 template <> __device__ __forceinline__ double distance<double>(double dx, double dy, double dz) {
   const double x = __builtin_fma(dx, dx, __builtin_fma(dy, dy, __builtin_fma(dz, dz, 1e-300)));
   const double y = __builtin_amdgcn_rsq(x);
-  const double g = x * y;
-  const double e = __builtin_fma(-g, y, 1.0);
-  return __builtin_fma(g * e, __builtin_fma(e, 0.375, 0.5), g);
+  const double h = 0.5 * y;
+  double g = x * y;
+  g = __builtin_fma(g, __builtin_fma(-h, g, 0.5), g);
+  return __builtin_fma(__builtin_fma(-g, g, x), h, g);
 }
 template <> __device__ __forceinline__ float distance<float>(float dx, float dy, float dz) {
   return __builtin_amdgcn_sqrtf(dx * dx + dy * dy + dz * dz);
 }
+
+// 2^-u as the kernels keep it until it multiplies a polynomial
+template <typename T> struct ExpOf { typedef T type; };
+template <> struct ExpOf<double> { typedef Exp2Parts type; };
 
 // distance() and exp2neg() of four pairs.  STAGED (FP64): step by step across the
 // four.  A dependent FP64 operation waits about 8 cycles and issues in 4, and the
@@ -320,12 +344,12 @@ template <> __device__ __forceinline__ float distance<float>(float dx, float dy,
 // that hold one wave per SIMD would wait half of the time.
 template <bool STAGED>
 __device__ __forceinline__ void distance_exp2neg4(const double (&dx)[4], const double (&dy)[4], const double (&dz)[4],
-                                                  double (&u)[4], double (&w)[4]) {
+                                                  double (&u)[4], Exp2Parts (&p)[4]) {
   if constexpr (!STAGED) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       u[r] = distance<double>(dx[r], dy[r], dz[r]);
-      w[r] = exp2neg<double>(u[r]);
+      p[r] = exp2neg_parts(u[r]);
     }
     return;
   }
@@ -339,28 +363,27 @@ __device__ __forceinline__ void distance_exp2neg4(const double (&dx)[4], const d
   BV_STEP(u[r] = __builtin_fma(dy[r], dy[r], u[r]));
   BV_STEP(u[r] = __builtin_fma(dx[r], dx[r], u[r]));
   BV_STEP(y[r] = __builtin_amdgcn_rsq(u[r]));
-  BV_STEP(u[r] = u[r] * y[r]);
-  BV_STEP(e[r] = __builtin_fma(-u[r], y[r], 1.0));
-  BV_STEP(t[r] = __builtin_fma(e[r], 0.375, 0.5));
-  BV_STEP(e[r] = u[r] * e[r]);
-  BV_STEP(u[r] = __builtin_fma(e[r], t[r], u[r]));
-  int m[4];
+  BV_STEP(t[r] = u[r] * y[r]);
+  BV_STEP(y[r] = 0.5 * y[r]);
+  BV_STEP(e[r] = __builtin_fma(-y[r], t[r], 0.5));
+  BV_STEP(t[r] = __builtin_fma(t[r], e[r], t[r]));
+  BV_STEP(e[r] = __builtin_fma(-t[r], t[r], u[r]));
+  BV_STEP(u[r] = __builtin_fma(e[r], y[r], t[r]));
   BV_STEP(e[r] = __builtin_fmin(u[r], kExpBound));
   BV_STEP(t[r] = kExpShift - e[r]);
-  BV_STEP(y[r] = t[r] - kExpShift; m[r] = low_word(t[r]));
+  BV_STEP(y[r] = t[r] - kExpShift; p[r].m = low_word(t[r]));
   BV_STEP(y[r] = -e[r] - y[r]);
-  BV_STEP(w[r] = __builtin_fma(0x1.e9d3fe3952179p-32, y[r], 0x1.e6063f7217bc6p-28));
-  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.b524fae627834p-24));
-  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.62bfd47773353p-20));
-  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.ffcbfc670dcd4p-17));
-  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.430913096fd9fp-13));
-  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.5d87fe78a5276p-10));
-  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.3b2ab6fba1ddap-7));
-  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.c6b08d704a0c2p-5));
-  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.ebfbdff82c598p-3));
-  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 0x1.62e42fefa39efp-1));
-  BV_STEP(w[r] = __builtin_fma(w[r], y[r], 1.0));
-  BV_STEP(w[r] = __builtin_amdgcn_ldexp(w[r], m[r]));
+  BV_STEP(p[r].w = __builtin_fma(0x1.e9d3fe3952179p-32, y[r], 0x1.e6063f7217bc6p-28));
+  BV_STEP(p[r].w = __builtin_fma(p[r].w, y[r], 0x1.b524fae627834p-24));
+  BV_STEP(p[r].w = __builtin_fma(p[r].w, y[r], 0x1.62bfd47773353p-20));
+  BV_STEP(p[r].w = __builtin_fma(p[r].w, y[r], 0x1.ffcbfc670dcd4p-17));
+  BV_STEP(p[r].w = __builtin_fma(p[r].w, y[r], 0x1.430913096fd9fp-13));
+  BV_STEP(p[r].w = __builtin_fma(p[r].w, y[r], 0x1.5d87fe78a5276p-10));
+  BV_STEP(p[r].w = __builtin_fma(p[r].w, y[r], 0x1.3b2ab6fba1ddap-7));
+  BV_STEP(p[r].w = __builtin_fma(p[r].w, y[r], 0x1.c6b08d704a0c2p-5));
+  BV_STEP(p[r].w = __builtin_fma(p[r].w, y[r], 0x1.ebfbdff82c598p-3));
+  BV_STEP(p[r].w = __builtin_fma(p[r].w, y[r], 0x1.62e42fefa39efp-1));
+  BV_STEP(p[r].w = p[r].w * y[r]);
 #undef BV_STEP
 }
 template <bool STAGED>

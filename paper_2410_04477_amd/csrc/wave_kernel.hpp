@@ -352,7 +352,8 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
     constexpr int I = decltype(I_c)::value, J = decltype(J_c)::value;
     const int j = J * 16 + lr;
     const T sj0 = su[j], sj1 = su[P + j], sj2 = su[2 * P + j];
-    T dx[4], dy[4], dz[4], u[4], e[4];
+    T dx[4], dy[4], dz[4], u[4];
+    typename ExpOf<T>::type e[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       dx[r] = ri[r][0] - sj0;
@@ -1060,7 +1061,8 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
         const int j = J * 16 + lr;
         const T sj0 = su[j], sj1 = su[P + j], sj2 = su[2 * P + j];
         T s1 = T(0), s2 = T(0), s3 = T(0);
-        T dx[4], dy[4], dz[4], u[4], e[4];
+        T dx[4], dy[4], dz[4], u[4];
+        typename ExpOf<T>::type e[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           dx[r] = ri[r][0] - sj0;

@@ -138,7 +138,8 @@ __global__ void __launch_bounds__(64, (rows_min_waves<G, COEF>())) bv_rows_kerne
   auto generate = [&](int I, int J, const double (&cj)[4][3]) __attribute__((always_inline)) {
     const int i = I * 16 + lr;
     const double si0 = su[i], si1 = su[P + i], si2 = su[2 * P + i];
-    double dx[4], dy[4], dz[4], u[4], e[4];
+    double dx[4], dy[4], dz[4], u[4];
+    Exp2Parts e[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       dx[r] = si0 - cj[r][0];
