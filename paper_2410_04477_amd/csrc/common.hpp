@@ -230,10 +230,8 @@ struct Exp2Parts {
 __device__ __forceinline__ double scaled(const Exp2Parts& e, double p) {
   return __builtin_amdgcn_ldexp(__builtin_fma(e.w, p, p), e.m);
 }
-__device__ __forceinline__ Exp2Parts exp2neg_parts(double x) {
-  x = __builtin_fmin(x, kExpBound);
-  const double t = kExpShift - x;
-  const double f = -x - (t - kExpShift);
+// 2^f - 1, |f| <= 1/2
+__device__ __forceinline__ double exp2m1(double f) {
   double q = 0x1.e9d3fe3952179p-32;
   q = __builtin_fma(q, f, 0x1.e6063f7217bc6p-28);
   q = __builtin_fma(q, f, 0x1.b524fae627834p-24);
@@ -245,7 +243,17 @@ __device__ __forceinline__ Exp2Parts exp2neg_parts(double x) {
   q = __builtin_fma(q, f, 0x1.c6b08d704a0c2p-5);
   q = __builtin_fma(q, f, 0x1.ebfbdff82c598p-3);
   q = __builtin_fma(q, f, 0x1.62e42fefa39efp-1);
-  return {q * f, low_word(t)};
+  return q * f;
+}
+__device__ __forceinline__ Exp2Parts exp2neg_parts(double x) {
+  x = __builtin_fmin(x, kExpBound);
+  const double t = kExpShift - x;
+  return {exp2m1(-x - (t - kExpShift)), low_word(t)};
+}
+// 2^-(x y), the product unrounded; past the bound (where 2^-(x y) is zero) x y < 2^40
+__device__ __forceinline__ double exp2neg_product(double x, double y) {
+  const double t = kExpShift - __builtin_fmin(x * y, kExpBound);
+  return scaled({exp2m1(__builtin_fma(-x, y, kExpShift - t)), low_word(t)}, 1.0);
 }
 template <typename T> __device__ __forceinline__ T exp2neg(T x);
 template <> __device__ __forceinline__ double exp2neg<double>(double x) { return scaled(exp2neg_parts(x), 1.0); }
@@ -398,29 +406,71 @@ __device__ __forceinline__ void distance_exp2neg4(const float (&dx)[4], const fl
 
 // ---- Bessel form of four pairs at once ---------------------------------------
 // K_v(x) = int_0^inf exp(-x cosh t) cosh(v t) dt by the trapezoidal rule with the
-// fixed step h = 1/6 for kBesselLo <= x <= kBesselMid, and h = 1/12 up to kBesselHi:
-// the discretisation error, about exp(x - pi^2 / h), is below 1e-16 there, the
-// rounding error of the sums at most 1.2e-15.  With a fixed step cosh t,
-// cosh(mu t), cosh((mu + 1) t) and t times their sinh depend on the node alone:
-// a workgroup forms them once, and a node costs one exponential and two products
-// (four with d / d nu).  12 to 50 nodes for the distances of neighbouring points,
-// 111 at x = 1e-6.  Rows kBesselNodes on are the nodes halfway, as far as
-// x > kBesselMid needs them (exp(-x (cosh t - 1)) < 1e-20 past the last).
+// fixed step h = 43/256 for kBesselLo <= x <= kBesselMid, and h / 2 up to kBesselHi:
+// the discretisation error, about exp(x - pi^2 / h), is below 3e-19 there.  With a
+// fixed step cosh t and the weights depend on the node alone: a workgroup forms
+// them once, and a node costs one exponential and two products (four with
+// d / d nu).  12 to 50 nodes for the distances of neighbouring points, 108 at
+// x = 1e-6.  Rows kBesselNodes on are the nodes halfway, as far as x > kBesselMid needs
+// them (exp(-x (cosh t - 1)) < 1e-20 past the last).
+// Rounding: the nodes are exact numbers, cosh(t) log2(e) is a rounded constant, and
+// the product with x enters the exponential unrounded; the sums run over even and
+// odd nodes apart.  Against 113-bit arithmetic rho is then off by 1.4e-16 to
+// 3e-16 in the mean (root of squares, nu up to 2) and 1e-15 at most for x in
+// [1e-3, 16], 1.2e-15 and 3e-15 up to 72; the functions above 1.6e-16 to 5e-16 and
+// 4e-15, 1.8e-15 and 1.1e-14.
 constexpr int kBesselNodes = 128, kBesselHalf = 14;
-constexpr int kBesselCols = 6;   // cosh t, h cosh(mu t), h cosh((mu + 1) t), h t sinh(mu t), h t sinh((mu + 1) t), a constant
-constexpr double kBesselStep = 1.0 / 6.0, kBesselLo = 6e-8, kBesselMid = 16.0, kBesselHi = 72.0;
+constexpr int kBesselCols = 6;   // log2(e) cosh t, the weights of K_mu and of the second order, of their derivatives, a constant
+constexpr double kBesselStep = 43.0 / 256.0, kBesselLo = 6e-8, kBesselMid = 16.0, kBesselHi = 72.0;
+constexpr double kBesselNear = 1.0 / 256.0;
 constexpr int kBesselBytes = (kBesselNodes + kBesselHalf) * kBesselCols * (int)sizeof(double);
 typedef const __attribute__((address_space(3))) double LdsDouble;
 
+// log2(e) cosh(k h), k = 0 .. 127, then log2(e) cosh((k + 1/2) h), k = 0 .. 13
+static __device__ const double kBesselCosh[kBesselNodes + kBesselHalf] = {
+    0x1.71547652b82fep+0, 0x1.768d5f615ce91p+0, 0x1.865de951e93f9p+0, 0x1.a1389229253b4p+0, 0x1.c7dfc40e6493dp+0,
+    0x1.fb6b54ca32a2dp+0, 0x1.1ea837d787692p+1, 0x1.47b6119b8d70dp+1, 0x1.7a086f5ebf3dfp+1, 0x1.b70ba0ffa22f3p+1,
+    0x1.003cae05e42fap+2, 0x1.2c329cc9106d5p+2, 0x1.60a5df5c4dcf9p+2, 0x1.9f122e75c64f0p+2, 0x1.e93b75fc3bda8p+2,
+    0x1.209d4e64294aep+3, 0x1.54c659d00f70dp+3, 0x1.92927cacafc9ap+3, 0x1.dbc11b4852385p+3, 0x1.193202e56fa43p+4,
+    0x1.4c7739efd9b70p+4, 0x1.892360c5f6903p+4, 0x1.d0edb6cda6269p+4, 0x1.12eefc6827557p+5, 0x1.452d89d97941ap+5,
+    0x1.809e442777926p+5, 0x1.c6ef7f289c582p+5, 0x1.0d0f26c499a07p+6, 0x1.3e4273272de26p+6, 0x1.7875d654eda5bp+6,
+    0x1.bd4eaab53199bp+6, 0x1.075faef89714cp+7, 0x1.378ac4b368776p+7, 0x1.70854f53807f0p+7, 0x1.b3ebd05ad5c00p+7,
+    0x1.01d31e359bc68p+8, 0x1.30fae3f3b97e5p+8, 0x1.68c29cdb255ffp+8, 0x1.aabe1d2a058cep+8, 0x1.f8cb157e6a682p+8,
+    0x1.2a8f4a92c49c1p+9, 0x1.612a82790133dp+9, 0x1.a1c28724b8c98p+9, 0x1.ee2afba12c4d5p+9, 0x1.2446856cc1530p+10,
+    0x1.59bb862b63d0bp+10, 0x1.98f782bab49a0p+10, 0x1.e3c44684f9bcap+10, 0x1.1e1fabfb5ee17p+11, 0x1.5274a479878bcp+11,
+    0x1.905bea2a42138p+11, 0x1.d995a5d0782dep+11, 0x1.1819fc0497bd6p+12, 0x1.4b54fb9dec5e8p+12, 0x1.87eeb5bfe4d1dp+12,
+    0x1.cf9de46d140f4p+12, 0x1.1234bfecbe06ap+13, 0x1.445bb5c9b8aa5p+13, 0x1.7faee96db21d3p+13, 0x1.c5dbd8ed0846bp+13,
+    0x1.0c6f48185df9ep+14, 0x1.3d880385918f3p+14, 0x1.779b90026c290p+14, 0x1.bc4e6176188a6p+14, 0x1.06c8e92ca2f63p+15,
+    0x1.36d91a305f479p+15, 0x1.6fb3b9dbc0d1fp+15, 0x1.b2f4629dda3c8p+15, 0x1.0140fb8e6103ap+16, 0x1.304e338b96230p+16,
+    0x1.67f67c7c8c505p+16, 0x1.a9ccc706f350bp+16, 0x1.f7adb66599cc9p+16, 0x1.29e68d8cb0ed7p+17, 0x1.6062f25dc525dp+17,
+    0x1.a0d67f3022eb7p+17, 0x1.ed13cf0abb0edp+17, 0x1.23a16a40b2585p+18, 0x1.58f83acecf3d3p+18, 0x1.9810815080e6ap+18,
+    0x1.e2b306a6c0fe8p+18, 0x1.1d7e0fb49a77cp+19, 0x1.51b579da27ec0p+19, 0x1.8f79c9379a7ffp+19, 0x1.d88a29729aa9dp+19,
+    0x1.177bc7df77b7ep+20, 0x1.4a99d82b95d2cp+20, 0x1.8711582f0642ep+20, 0x1.ce980a21a6b15p+20, 0x1.1199e08d36b06p+21,
+    0x1.43a482f72144fp+21, 0x1.7ed634dccfd01p+21, 0x1.c4db81bebc4b0p+21, 0x1.0bd7ab49f6b2dp+22, 0x1.3cd4abe0a33f6p+22,
+    0x1.76c76b269049ap+22, 0x1.bb536f89fbe19p+22, 0x1.06347d4dd2754p+23, 0x1.362988e3dc12ap+23, 0x1.6ee40c1525e0bp+23,
+    0x1.b1feb8d75ac2cp+23, 0x1.00afaf6916e0cp+24, 0x1.2fa2543d0bea1p+24, 0x1.672b2db904a4ep+24, 0x1.a8dc48ede3cafp+24,
+    0x1.f6913be1c9957p+24, 0x1.293e4c5209b11p+25, 0x1.5f9beb0f1cb80p+25, 0x1.9feb10e7a8b35p+25, 0x1.ebfd5158763d5p+25,
+    0x1.22fcb39bd57b2p+26, 0x1.583563e652953p+26, 0x1.972a079260277p+26, 0x1.e1a26582ce6cdp+26, 0x1.1cdcd090a3c92p+27,
+    0x1.50f6bcc5864fbp+27, 0x1.8e982950acf5bp+27, 0x1.d77f4547b26c9p+27, 0x1.16dded8e5f1d7p+28, 0x1.49df1ed226c28p+28,
+    0x1.863477fc0ac98p+28, 0x1.cd92c404b4a2fp+28, 0x1.10ff58c59d5fep+29, 0x1.42edb7b74dbf1p+29, 0x1.7dfdfac75cf31p+29,
+    0x1.c3dbbb6b45cdap+29, 0x1.0b40642506a19p+30, 0x1.3c21b98d62585p+30, 0x1.72a219e3904f6p+0, 0x1.7d1d5b6f0007cp+0,
+    0x1.925fc05dfcb0bp+0, 0x1.b30331bd22b98p+0, 0x1.dff3fa0f80787p+0, 0x1.0d3bb9fc782d6p+1, 0x1.321a9ed8bd513p+1,
+    0x1.5fa199ef32304p+1, 0x1.971a4545eb1fep+1, 0x1.da1638ca18024p+1, 0x1.153d32dae553bp+2, 0x1.454666b033747p+2,
+    0x1.7e827b6168551p+2, 0x1.c28fccebdee2ep+2};
+
 // The table of one order by the 64 lanes of a wave; the caller orders the LDS accesses.
+// The second order is mu + 1, or 1 - mu for nu < 1/2 (K_(nu-1) = K_(1-nu), which
+// the recurrence downwards would get by a cancellation).
 __device__ inline void bessel_table(double* tab, const BesselOrder& o, int ln) {
   for (int k = ln; k < kBesselNodes + kBesselHalf; k += 64) {
-    const double t = (k < kBesselNodes ? k : k - kBesselNodes + 0.5) * kBesselStep;
+    const double t = (k < kBesselNodes ? k : k - kBesselNodes + 0.5) * kBesselStep;   // exact
     const double w = k == 0 ? 0.5 * kBesselStep : kBesselStep;
-    const double e = exp(t), em = exp(o.mu * t);
-    const double p = em * e, ei = 1.0 / e, emi = 1.0 / em, pi = 1.0 / p;
+    const double a = o.mu * t, e = exp(t);
+    double em = exp(a);
+    em = __builtin_fma(em, __builtin_fma(o.mu, t, -a), em);   // e^(mu t) for the exact product
+    const double p = o.n == 0 ? e / em : em * e, emi = 1.0 / em, pi = 1.0 / p;
     double* row = tab + k * kBesselCols;
-    row[0] = 0.5 * (e + ei);
+    row[0] = kBesselCosh[k];
     row[1] = w * 0.5 * (em + emi);
     row[2] = w * 0.5 * (p + pi);
     row[3] = w * t * 0.5 * (em - emi);
@@ -434,8 +484,9 @@ __device__ inline void bessel_table(double* tab, const BesselOrder& o, int ln) {
 // d rho / d nu.  One copy for all tiles of a kernel (a copy per tile made the
 // kernels 90 to 460 KB); the results come back in registers.  Bound by the FP64
 // operations of the exponentials: 2,000 blocks, m = 30, d l / d range and d l / d nu
-// 520 us, one distance at a time with its own step (about 110 nodes at
-// x = 1e-4, all weights recomputed, arrays in scratch) 1,112 us.  Outside
+// 1,112 us one distance at a time with its own step (about 110 nodes at
+// x = 1e-4, all weights recomputed, arrays in scratch), 514 us with a rounded
+// exponent (rho off by up to 1e-14), 536 us now.  Outside
 // [kBesselLo, kBesselHi] the functions above are called, lane by lane.
 typedef double BesselOut __attribute__((ext_vector_type(8)));
 typedef double Bessel4 __attribute__((ext_vector_type(4)));
@@ -444,66 +495,75 @@ __device__ __noinline__ inline BesselOut bessel4(Bessel4 x, LdsDouble* tab) {
   constexpr bool DNU = WHAT == 2;
   const int order = (int)tab[kBesselCols + 5];
   const double mu = tab[5], lognorm = tab[2 * kBesselCols + 5], dlognorm = tab[3 * kBesselCols + 5];
-  double u[4], k0[4], k1[4], d0[4], d1[4];
-  bool rare = false, half = false;
+  // The smallest distance of the wave sets the number of nodes, 6 log(80 / x), where
+  // Temme's series takes 15 terms for any x <= 2: below kBesselNear (58 nodes, where
+  // both cost the same), if no distance of the wave exceeds 2, the series serves them
+  // all (g of nu < 1/2 excepted, which it has by a cancellation).  20,000 points
+  // of which every second lies within 1e-7 of another, range 0.1, m = 30, value / value
+  // and gradient: 389 / 1,103 us with nodes throughout, 311 / 846 us so.  (With the line
+  // at 1/32 for g points without such neighbours take 642 instead of 614 us.)
+  // sums over the even ([0]) and the odd nodes apart; with the derivatives in the order
+  // over all (the gradient kernel of G = 3 would lose its second wave)
+  constexpr int ODD = DNU ? 0 : 1;
+  double z[4], k0[2][4], k1[2][4], d0[4], d1[4], last[4];
+  bool rare = false, half = false, near = false, far = false;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const bool in = x[r] >= kBesselLo && x[r] <= kBesselHi;
     rare |= !in & (x[r] > 1e-140);
     half |= in & (x[r] > kBesselMid);
-    u[r] = (in ? x[r] : 1.0) * kLog2E;
-    k0[r] = k1[r] = d0[r] = d1[r] = 0.0;
+    near |= in & (x[r] < kBesselNear);
+    far |= x[r] > 2.0;
+    z[r] = in ? x[r] : 1.0;
+    k0[0][r] = k1[0][r] = k0[1][r] = k1[1][r] = d0[r] = d1[r] = 0.0;
   }
-  auto node = [&](LdsDouble* row) __attribute__((always_inline)) {
+  auto node = [&](LdsDouble* row, int s) __attribute__((always_inline)) {
     const double ch = row[0], c0 = row[1], c1 = row[2], s0 = row[3], s1 = row[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const double e = exp2neg<double>(u[r] * ch);
-      k0[r] = __builtin_fma(e, c0, k0[r]);
-      k1[r] = __builtin_fma(e, c1, k1[r]);
+      const double e = exp2neg_product(z[r], ch);
+      k0[s][r] = __builtin_fma(e, c0, k0[s][r]);
+      k1[s][r] = __builtin_fma(e, c1, k1[s][r]);
       if (DNU) {
         d0[r] = __builtin_fma(e, s0, d0[r]);
         d1[r] = __builtin_fma(e, s1, d1[r]);
       }
+      last[r] = e * s1;
     }
   };
+  const bool series = __any(near) && !__any(far) && (WHAT == 0 || (WHAT == 1 && order > 0));   // the same in every lane
   if (__any(half)) {
     // the nodes halfway first: their sums count for x > kBesselMid only, and both
     // sets then weigh one half
 #pragma nounroll
-    for (int k = kBesselNodes; k < kBesselNodes + kBesselHalf; ++k) node(tab + k * kBesselCols);
+    for (int k = kBesselNodes; k < kBesselNodes + kBesselHalf; ++k) node(tab + k * kBesselCols, 0);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const bool take = u[r] > kBesselMid * kLog2E;
-      k0[r] = take ? k0[r] : 0.0;
-      k1[r] = take ? k1[r] : 0.0;
+      const bool take = z[r] > kBesselMid;
+      k0[0][r] = take ? k0[0][r] : 0.0;
+      k1[0][r] = take ? k1[0][r] : 0.0;
       d0[r] = take ? d0[r] : 0.0;
       d1[r] = take ? d1[r] : 0.0;
     }
   }
 #pragma nounroll
-  for (int k = 0; k < kBesselNodes; k += 4) {
+  for (int k = 0; k < kBesselNodes && !series; k += 4) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) node(tab + (k + q) * kBesselCols);
-    // past t = 1 t sinh((mu + 1) t) exceeds a third of every other weight of a node
-    const double ch = tab[(k + 3) * kBesselCols], s1 = tab[(k + 3) * kBesselCols + 4];
+    for (int q = 0; q < 4; ++q) node(tab + (k + q) * kBesselCols, q & ODD);
+    // past t = 1 t sinh of the second order exceeds a third of every other weight of a node
     bool more = k < 4;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) more |= exp2neg<double>(u[r] * ch) * s1 > 1e-19 * k1[r];
+    for (int r = 0; r < 4; ++r) more |= last[r] > 1e-19 * k1[ODD][r];
     if (!__any(more)) break;
   }
   const double nu = mu + order;
   BesselOut out = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const double w = u[r] > kBesselMid * kLog2E ? 0.5 : 1.0;
-    const double z = u[r] * kLn2, zi = 1.0 / z;
-    double klo = k0[r], khi = k1[r], dlo = d0[r], dhi = d1[r];   // K_(nu-1), K_nu, their derivatives in nu
-    if (order == 0) {
-      klo = k1[r] - (2.0 * mu * zi) * k0[r];
-      khi = k0[r];
-      dhi = d0[r];
-    }
+    const double w = z[r] > kBesselMid ? 0.5 : 1.0, zi = 1.0 / z[r];
+    const double a0 = k0[0][r] + k0[1][r], a1 = k1[0][r] + k1[1][r];
+    double klo = order == 0 ? a1 : a0, khi = order == 0 ? a0 : a1;   // K_(nu-1), K_nu
+    double dlo = d0[r], dhi = order == 0 ? d0[r] : d1[r];   // their derivatives in nu
     for (int v = 1; v < order; ++v) {
       const double f = 2.0 * (mu + v) * zi;
       const double kn = klo + f * khi;
@@ -515,15 +575,15 @@ __device__ __noinline__ inline BesselOut bessel4(Bessel4 x, LdsDouble* tab) {
       klo = khi;
       khi = kn;
     }
-    const double logx = log(z);
+    const double logx = log(z[r]);
     const double c = w * exp(lognorm + nu * logx);
     const bool at0 = x[r] <= 1e-140;   // a coincident pair (distance<double> gives 1e-150)
-    const double nan = x[r] - x[r];    // 0, or NaN for the distance of a point that is not finite
+    const double nan = x[r] - x[r];    // 0, or NaN for a NaN distance
     if (WHAT == 0) out[r] = at0 ? 1.0 : c * khi + nan;
-    if (WHAT >= 1) out[r] = at0 ? 0.0 : c * z * klo + nan;
+    if (WHAT >= 1) out[r] = at0 ? 0.0 : c * z[r] * klo + nan;
     if (DNU) out[r + 4] = at0 ? 0.0 : c * (khi * (logx + dlognorm) + dhi) + nan;
   }
-  if (__any(rare)) {
+  if (series || __any(rare)) {
     BesselOrder o;
     o.mu = mu;
     o.n = order;
@@ -536,7 +596,7 @@ __device__ __noinline__ inline BesselOut bessel4(Bessel4 x, LdsDouble* tab) {
     o.mu_pi_csc = tab[8 * kBesselCols + 5];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (x[r] > 1e-140 && !(x[r] >= kBesselLo && x[r] <= kBesselHi)) {
+      if (x[r] > 1e-140 && (series || !(x[r] >= kBesselLo && x[r] <= kBesselHi))) {
         double rho, g, dn = 0.0;
         if (DNU) matern_general_dnu(x[r], o, &rho, &g, &dn);
         else matern_general(x[r], o, &rho, &g);
