@@ -572,8 +572,13 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   // block, z, once per panel (10 operations) and v[I] = sum_c A[row][c] z[c], 4
   // products per row tile.  The substitution by rows costs fewer operations but
   // needs its results written to LDS and read back in this layout, one more
-  // exchange in each panel's chain of dependent steps.
+  // exchange in each panel's chain of dependent steps.  Products with the inverse add
+  // about 10 % to the rounding error of a block; up to G = 3, where that is the largest
+  // part of it and a panel has one or two row tiles, each lane substitutes along its row
+  // instead and keeps one of the four results (SUBST; joint sizes to 33: per-block
+  // error 3.8e-14 -> 3.35e-14, value at n = 2,000 17.8 us either way).
   constexpr bool ROWPAN = sizeof(T) == 8 && !LEFT && !TIGHT;
+  constexpr bool SUBST = G <= 3;
   auto publish_rows = [&](auto Kc_c, int c0) __attribute__((always_inline)) {
     constexpr int Kc = decltype(Kc_c)::value;
     if (lr >= c0 && lr < c0 + 4) {
@@ -597,7 +602,7 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
       for (int c = 0; c <= r; ++c) D[r][c] = pan[(k0 + r) * 4 + c];
   };
   // Cholesky of the block (same values in every lane), pivots to LDS; z = -(row
-  // lg of the inverse), the sign for the panel's -A
+  // lg of the inverse), the sign for the panel's -A; SUBST: z = 1 / (the factor's diagonal)
   auto factor_block = [&](int k0, T (&D)[4][4], T (&z)[4]) __attribute__((always_inline)) {
     if (k0 + 4 > p) {   // columns at and beyond p: identity
 #pragma unroll
@@ -620,12 +625,17 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
         D[r][c] = -D[r][c] * rinv[c];
       }
     }
+    if constexpr (SUBST) {
 #pragma unroll
-    for (int c = 3; c >= 0; --c) {
-      T v = lg == c ? T(-1) : T(0);
+      for (int c = 0; c < 4; ++c) z[c] = rinv[c];
+    } else {
 #pragma unroll
-      for (int j = c + 1; j < 4; ++j) v -= z[j] * D[j][c];
-      z[c] = v * rinv[c];
+      for (int c = 3; c >= 0; --c) {
+        T v = lg == c ? T(-1) : T(0);
+#pragma unroll
+        for (int j = c + 1; j < 4; ++j) v -= z[j] * D[j][c];
+        z[c] = v * rinv[c];
+      }
     }
     if (ln == 0) {
 #pragma unroll
@@ -633,7 +643,7 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
     }
   };
   // v[I] (and ve, the appended rows) of the published panel; border entries to LDS
-  auto solve_rows = [&](auto K_c, int k0, const T (&z)[4], T (&v)[G], T& ve) __attribute__((always_inline)) {
+  auto solve_rows = [&](auto K_c, int k0, const T (&D)[4][4], const T (&z)[4], T (&v)[G], T& ve) __attribute__((always_inline)) {
     BV_CV(K);
     // the next row tile's entries are read before the current one's products
     // (no more: the scheduler would read all of them first and spill)
@@ -642,13 +652,28 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
 #pragma unroll
       for (int c = 0; c < 4; ++c) d[c] = pan[row * 4 + c];
     };
-    auto dot = [&]() __attribute__((always_inline)) { return cur[0] * z[0] + cur[1] * z[1] + (cur[2] * z[2] + cur[3] * z[3]); };
+    auto solved = [&]() __attribute__((always_inline)) {   // entry lg of the solved row, from its published entries cur
+      if constexpr (SUBST) {
+        T x[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          x[c] = -cur[c];
+#pragma unroll
+          for (int j = 0; j < c; ++j) x[c] -= x[j] * D[c][j];
+          x[c] *= z[c];
+        }
+        const T lo = lg & 1 ? x[1] : x[0], hi = lg & 1 ? x[3] : x[2];
+        return lg & 2 ? hi : lo;
+      } else {
+        return cur[0] * z[0] + cur[1] * z[1] + (cur[2] * z[2] + cur[3] * z[3]);
+      }
+    };
     fetch(16 * K + lr, cur);
     static_for<K, G + (EINV ? 1 : 0)>(BV_CI(I) {
       BV_CV(I);
       if constexpr (I + 1 < G + (EINV ? 1 : 0)) fetch((I + 1) * 16 + lr, nxt);
-      if constexpr (I < G) v[I] = dot();
-      else ve = dot();
+      if constexpr (I < G) v[I] = solved();
+      else ve = solved();
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int c = 0; c < 4; ++c) cur[c] = nxt[c];
@@ -657,9 +682,8 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
     // beyond p have entries in rows from p on only, which nothing reads)
     if (lr < k0 - 16 * K + lg) v[K] = T(0);
     // the border row's entries of the four columns
-    T w = T(0);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) w += pan[p * 4 + c] * z[c];
+    fetch(p, cur);
+    const T w = solved();
     if (lr == 0) swk[k0 + lg] = w;
   };
 
@@ -710,7 +734,7 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
         const int k0 = K * 16 + c0;
         T z[4], v[G], ve = T(0);
         factor_block(k0, D, z);
-        solve_rows(K_c, k0, z, v, ve);
+        solve_rows(K_c, k0, D, z, v, ve);
         const bool next = c0 + 4 < 16 && k0 + 4 < kend;
         if (MODE == 4 ? c0 + 4 < 16 : next) {   // (prediction: the block's columns may start in this tile)
           static_for<K, G>(BV_CI(I) {
