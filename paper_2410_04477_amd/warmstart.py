@@ -87,10 +87,13 @@ class MLP:
         return g
 
     def train_step(self, X: torch.Tensor, T: torch.Tensor, lr: float) -> torch.Tensor:
-        if self.bf16 and X.dim() == 2 and X.shape[1] == SIZES[0] and T.numel() == X.shape[0] * SIZES[3]:
-            # the same operations in one call
+        own = all(getattr(getattr(self, f), "__func__", None) is getattr(MLP, f) for f in ("forward", "backward"))
+        if own and self.bf16 and X.dim() == 2 and X.shape[1] == SIZES[0] and 0 < X.shape[0] <= 1 << 20 \
+                and T.numel() == X.shape[0] * SIZES[3] and X.dtype == T.dtype == torch.float32:
+            # the same operations in one call; the step counts once it is accepted
+            part = api.mlp_step(X, T, SIZES, self.params, self.m, self.v, self.step_count + 1, lr)
             self.step_count += 1
-            return api.mlp_step(X, T, SIZES, self.params, self.m, self.v, self.step_count, lr)
+            return part
         out, cache = self.forward(X)
         dout = torch.empty_like(out)
         part = api.mse(out, T, dout)
