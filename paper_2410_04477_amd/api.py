@@ -383,7 +383,21 @@ def mlp_step(X: torch.Tensor, target: torch.Tensor, sizes: Sequence[int], params
              m: Sequence[torch.Tensor], v: Sequence[torch.Tensor], step: int, lr: float = 1e-3, beta1: float = 0.9,
              beta2: float = 0.999, eps: float = 1e-8, nparts: int = 8) -> torch.Tensor:
     """One training step of a three-layer ReLU network (vecchia_mlp_step); params,
-    m and v are updated in place.  Returns the loss parts."""
+    m and v are updated in place.  Returns the loss parts.  The kernels read and write by
+    sizes, so every shape and type is checked against them."""
+    sizes = [int(s) for s in sizes]
+    if len(sizes) != 4:
+        raise ValueError("sizes must be four layer widths")
+    if any(t.dtype != torch.float32 for t in (X, target, *params, *m, *v)):
+        raise ValueError("tensors must be float32")
+    if X.dim() != 2 or X.shape[1] != sizes[0]:
+        raise ValueError(f"X must be (batch, {sizes[0]})")
+    if target.numel() != X.shape[0] * sizes[3]:
+        raise ValueError(f"target must hold {sizes[3]} values per row of X")
+    want = [w for a, b in zip(sizes[:-1], sizes[1:]) for w in (a * b, b)]
+    for name, ts in (("params", params), ("m", m), ("v", v)):
+        if [t.numel() for t in ts] != want:
+            raise ValueError(f"{name} must be weight (out, in) and bias of each of the three layers")
     _dev_check(X, target, *params, *m, *v)
     lib = L.lib()
     n = (ctypes.c_int32 * 4)(*sizes)

@@ -1,6 +1,7 @@
-"""The training step's bookkeeping and its route, without a GPU: a batch that is refused
-leaves the step count alone (it enters Adam's bias correction), and a subclass's own
-forward and backward are called."""
+"""The training step's bookkeeping, route and argument checks, without a GPU: a batch that
+is refused leaves the step count alone (it enters Adam's bias correction), a subclass's own
+forward and backward are called, and every shape and type the kernels rely on is
+checked before the call."""
 import pytest
 import torch
 
@@ -34,3 +35,29 @@ def test_overridden_methods_are_called(monkeypatch):
     net = Sub(1, "cpu")
     net.train_step(torch.zeros(4, 96), torch.zeros(4, 3), 1e-3)
     assert calls == ["forward", "backward"] + ["adam"] * 6 and net.step_count == 1
+
+
+def _case(**change):
+    z = lambda *s, dt=torch.float32: torch.zeros(*s, dtype=dt)
+    shapes = [(16, 12), (16,), (16, 16), (16,), (3, 16), (3,)]
+    kw = dict(X=z(5, 12), target=z(5, 3), sizes=(12, 16, 16, 3), params=[z(*s) for s in shapes],
+              m=[z(*s) for s in shapes], v=[z(*s) for s in shapes], step=1)
+    kw.update(change)
+    return kw
+
+
+Z = torch.zeros
+
+
+@pytest.mark.parametrize("change", [
+    dict(X=Z(5, 11)), dict(X=Z(60)), dict(X=Z(5, 12, dtype=torch.float64)), dict(target=Z(4, 3)), dict(target=Z(5, 2)),
+    dict(target=Z(5, 3, dtype=torch.float16)), dict(sizes=(12, 16, 3)), dict(params=_case()["params"][:5]),
+    dict(m=_case()["m"][:4] + [Z(3, 15), Z(3)]), dict(v=[Z(16, 12, dtype=torch.float64)] + _case()["v"][1:])])
+def test_shapes_and_types_are_checked(change):
+    with pytest.raises(ValueError, match="sizes|float32|batch|values per row|weight"):
+        api.mlp_step(**_case(**change))
+
+
+def test_well_formed_arguments_reach_the_device_check():
+    with pytest.raises(ValueError, match="HIP device"):
+        api.mlp_step(**_case())
