@@ -567,7 +567,7 @@ bool mlp_sizes_ok(int64_t b, const int32_t* n) {
   if (!n || b <= 0 || b > (1 << 20)) return false;
   for (int q = 0; q < 4; ++q)
     if (n[q] <= 0 || n[q] > 16384) return false;
-  return true;
+  return b * n[3] < ((int64_t)1 << 31) - (1 << 24);   // the loss kernel counts the outputs in 32 bits
 }
 // C (M x N) = op(A) op(B), all row-major without gaps
 GemmArgs mlp_gemm(const float* A, const float* B, float* C, int M, int N, int K, int ta, int tb) {
@@ -608,6 +608,7 @@ extern "C" int vecchia_mlp_step(const float* X, const float* target, int32_t bat
                                 void* workspace, size_t ws_bytes, void* stream) {
   if (!X || !target || !params || !m || !v || !loss_part || !workspace || nparts <= 0 || step < 1) return VECCHIA_EINVAL;
   if (!mlp_sizes_ok(batch, sizes)) return VECCHIA_EINVAL;
+  if ((int64_t)batch * sizes[3] + 256 * (int64_t)nparts > INT32_MAX) return VECCHIA_EINVAL;   // and in strides of its grid
   for (int q = 0; q < 6; ++q)
     if (!params[q] || !m[q] || !v[q]) return VECCHIA_EINVAL;
   const MlpLayout L = mlp_layout(batch, sizes);

@@ -2,6 +2,9 @@
 is refused leaves the step count alone (it enters Adam's bias correction), a subclass's own
 forward and backward are called, and every shape and type the kernels rely on is
 checked before the call."""
+import ctypes
+import os
+
 import pytest
 import torch
 
@@ -61,3 +64,13 @@ def test_shapes_and_types_are_checked(change):
 def test_well_formed_arguments_reach_the_device_check():
     with pytest.raises(ValueError, match="HIP device"):
         api.mlp_step(**_case())
+
+
+@pytest.mark.skipif(not os.path.exists(os.path.join(os.path.dirname(api.__file__), "libvecchia.so")), reason="library not built")
+@pytest.mark.parametrize("batch,width,ok", [(256, 3, True), (1 << 20, 2031, True), (1 << 20, 2047, False),
+                                            (1 << 20, 16384, False), (65536, 16384, True), (131072, 16384, False)])
+def test_outputs_are_counted_in_32_bits(batch, width, ok):
+    """More outputs than the loss kernel counts (2^31, less the strides of its grid) have no workspace size."""
+    from paper_2410_04477_amd import _lib as L
+    size = L.lib().vecchia_mlp_step_workspace_size(batch, (ctypes.c_int32 * 4)(16, 16, 16, width))
+    assert (size > 0) == ok
