@@ -263,7 +263,10 @@ size_t vecchia_plan_workspace_size(int64_t bc, int32_t max_theta);
  * kernel, FP32, G = 9 tile rows, mode 5: gradient with the factor kept in
  * registers; mode 1: through the tile buffer; "...,2>+...,3>": the split
  * gradient, factorisation then adjoint; "...,6>+...,3>": the same with the
- * left-looking factorisation).  Host only.  VECCHIA_EINVAL for a bad
+ * left-looking factorisation; bv_rows_kernel: the FP64 value at G = 7 to
+ * 10).  The name is that of the closed-form orders nu; in FP64 the Bessel form
+ * runs bv_wave_kernel for all values, and mode 1 for the left-looking
+ * gradient.  Host only.  VECCHIA_EINVAL for a bad
  * class index, VECCHIA_ENOMEM if cap bytes cannot hold the name. */
 int vecchia_plan_class_kernel(const vecchia_plan* plan, int32_t q, int32_t precision, int32_t with_grad,
                               char* name, int32_t cap);
@@ -310,7 +313,8 @@ int vecchia_plan_timing(vecchia_plan* plan, double* ms, int64_t* launches, int r
  *   counters     out or NULL, 2*ntheta int32: [t*2+0] blocks re-factorised in
  *                FP64 by the FP32 guard, [t*2+1] blocks that were not positive
  *                definite even in FP64 (then loglik[t] is NaN); a block with a
- *                coordinate that is not finite is one of them
+ *                coordinate that is not finite is one of them (an observation
+ *                that is not finite makes its blocks -inf or NaN, not counted)
  *   partial      out or NULL, ntheta*bc doubles: per-block terms l_i,
  *                [t*bc + i]
  * The FP32 guard flags a block when a pivot d_k (the diagonal before the

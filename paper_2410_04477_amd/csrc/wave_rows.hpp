@@ -28,7 +28,9 @@ namespace bv {
 // waits in LDS, and its updates are applied to every other tile as that is generated.
 template <int G> constexpr int rows_deferred() { return G >= 10 ? 1 : 0; }
 template <int G, bool COEF> constexpr int rows_min_waves() {
-  // the most that leave the weights without scratch (G = 5: 100 bytes); the value has G >= 7 only
+  // the most at which the weights keep nearly all tiles in registers (bytes of scratch per
+  // lane: 100 at G = 5, 20, 412, 924 and 956 at G = 7 to 10, where one wave has all
+  // registers already); the value has G >= 7 only (none, 12 at G = 10)
   return G <= 2 ? 4 : G <= 3 ? 3 : G <= 5 ? 2 : 1;
 }
 // LDS elements: coordinates, y, pivots, border row, the published columns, the first
