@@ -3,7 +3,7 @@
 // centroid (Alg. 1, nearest neighbours).  Untimed in the paper's convention.
 //
 // K-means: Lloyd iterations in FP64.  Assignment walks a grid of cells that
-// lists the centroids (below 128 blocks it is exhaustive over the centroids,
+// lists the centroids (below 1,024 blocks it is exhaustive over the centroids,
 // staged through LDS); both are exact, ties go to the lower index.  Centroid sums
 // use 64-bit fixed point (exact integer atomics), so every run produces the same
 // centroids bit for bit.
@@ -110,11 +110,18 @@ struct KmArgs {
 // in cell order once, so that the lanes of a wave walk the same cells.
 // n = 2e5, 20,000 blocks in 2-D: one assignment 2.04 ms exhaustive (2e12
 // distances/s).
-constexpr int64_t kKmGridMinBlocks = 128;   // below, the exhaustive kernel's few rounds cost less than the cell walk
-// and above, the walk is taken while the lists it visits hold fewer than a
-// quarter of the centroids: a step of a list waits for memory, a step of the
-// exhaustive kernel reads LDS
-constexpr int64_t kKmWalkRatio = 4;
+// Below 1,024 blocks the exhaustive kernel is the faster one: 20 iterations, n = 200,000
+// in 2-D, exhaustive / cell walk 4.5 / 10.3 ms at 128 blocks, 3.1 / 5.7 at 256, 2.5 / 3.5
+// at 512, 2.6 / 2.7 at 768, 2.8 / 2.5 at 1,024, 5.0 / 1.9 at 2,048 (3-D 2.9 / 2.8 at
+// 1,024; n = 5,000 1.0 / 0.75).  The points of a wave in cell order also add to the same
+// few sums, which the fewer blocks make the worse.
+constexpr int64_t kKmGridMinBlocks = 1024;
+// Above, the walk is taken while the lists it visits hold fewer than a 16th of the
+// centroids: a step of a list waits for memory, a step of the exhaustive kernel reads
+// LDS.  n = 100,000 with part of the points in a clump, exhaustive / cell walk:
+// 3.1 / 2.1 ms where the lists hold 0.062 (2,000 blocks), 10.4 / 8.9 at 0.041 and 10.4 / 12.2
+// at 0.071 (8,000 blocks), 2.0 / 2.4 at 0.12 (1,024), 3.1 / 4.2 at 0.14 (2,000).
+constexpr int64_t kKmWalkRatio = 16;
 
 struct KmGrid {
   double lo[3];
