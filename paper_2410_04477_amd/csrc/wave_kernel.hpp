@@ -197,7 +197,11 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   // The FP64 gradient at G = 9 (45 tiles, 360 registers, with the right-hand sides'
   // working set) fits the registers without scratch only with masks instead of
   // branches in the generation, the panel kept by columns and one nest of updates.
-  constexpr bool TIGHT = sizeof(T) == 8 && MODE == 5 && G == 9;
+  // The value at G = 11 and the prediction from G = 10 on (Bessel form: 11) exceed them
+  // either way, and spill less so: 3,000 blocks, value at G = 11 610 us by rows
+  // (with 752 bytes of scratch), 464 so (612; 521 before the row panels); prediction at G = 11 766 and 563 us
+  // (1,220 and 868), at G = 10 387 and 325 us (612 and 356), but at G = 9 224 and 256 us.
+  constexpr bool TIGHT = sizeof(T) == 8 && ((MODE == 5 && G == 9) || ((MODE == 0 || MODE == 4) && G >= (GEN ? 11 : 10)));
   constexpr bool STAGED = wave_min_waves<T, G, MODE, GEN>() == 1;
   T* work = su + 3 * P;
   // MODE 5 appends 16 rows to the panel (the identity rows whose elimination
@@ -406,13 +410,11 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
     }
     // Where the tiles outgrow the VGPRs the finished tile goes to the accumulator
     // registers now, so that the generated values do not pile up until the first
-    // update: by D = 0 * 0 + C, or (the FP64 value kernels, whose first 32 tiles
-    // fill the accumulator registers) by asking for the move itself; not with the
-    // Bessel form, where tiles asked for like this did not survive the calls.
+    // update: by D = 0 * 0 + C.  (Asking for the move itself is cheaper, but where other
+    // tiles are in scratch the compiler lost tiles asked for like this: with the
+    // calls of the Bessel form, and at G = 11.)
     constexpr bool ONE = sizeof(T) == 8 && wave_min_waves<T, G, MODE, GEN>() == 1;
-    if constexpr (ONE && MODE == 0 && !GEN) {
-      if constexpr (tix(I, J) < 32) asm volatile("" : "+a"(acc[tix(I, J)]));
-    } else if constexpr (sizeof(T) == 8 ? ONE || (LEFT && G == 10) : !(G <= 9 && (MODE == 5 || MODE == 2))) {
+    if constexpr (sizeof(T) == 8 ? ONE || (LEFT && G == 10) : !(G <= 9 && (MODE == 5 || MODE == 2))) {
       acc[tix(I, J)] = M::op(T(0), T(0), acc[tix(I, J)]);
     }
   };
