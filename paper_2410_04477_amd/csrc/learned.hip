@@ -302,6 +302,30 @@ __global__ void __launch_bounds__(GEMM_T) gemm_bf16_kernel(GemmArgs g) {
   gemm_tile(g, blockIdx.y * 16, blockIdx.x * 16, lds);
 }
 
+// One wave per tile and one step at a time: the same products in the same order.
+__global__ void __launch_bounds__(64) gemm_bf16_wave_kernel(GemmArgs g) {
+  const int l = threadIdx.x, row = l & 15, kq = (l >> 4) * 4;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 0; k0 < g.K; k0 += 16) {
+    bf16x4 a, b;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      a[j] = f32_to_bf16_rne(ldA(g, m0 + row, k0 + kq + j));
+      b[j] = f32_to_bf16_rne(ldB(g, k0 + kq + j, n0 + row));
+    }
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) gemm_epilogue(g, m0 + kq + r, n0 + row, acc[r]);
+}
+// With fewer than eight steps two or three of a workgroup's four waves have nothing to
+// load; once the tiles fill the chip several times over, one wave per tile is the faster
+// kernel: M x 256 x K, four waves / one wave, 20,000 x 32 50 / 25 us, x 64 55 / 44,
+// x 96 66 / 64, x 128 79 / 83; 4,096 x 32 13.5 / 8.4, x 96 18.8 / 16.6, and 2,000 x 96
+// (2,000 tiles) 11.1 / 10.8 and with A transposed 8.7 / 11.0.
+constexpr int GEMM_WAVE_K = 128, GEMM_WAVE_TILES = 4096;
+
 // FP32 reference mode: 16 x 16 tile per 256 threads, plain FMAs
 __global__ void __launch_bounds__(256) gemm_f32_kernel(GemmArgs g) {
   const int n = blockIdx.x * 16 + (threadIdx.x & 15);
@@ -498,7 +522,9 @@ extern "C" int vecchia_gemm(const float* A, const float* B, float* C, const floa
   g.act = act;
   g.beta_accum = accumulate;
   const dim3 grid((N + 15) / 16, (M + 15) / 16);
-  if (use_bf16)
+  if (use_bf16 && K < GEMM_WAVE_K && (int64_t)grid.x * grid.y >= GEMM_WAVE_TILES)
+    hipLaunchKernelGGL(gemm_bf16_wave_kernel, grid, dim3(64), 0, (hipStream_t)stream, g);
+  else if (use_bf16)
     hipLaunchKernelGGL(gemm_bf16_kernel, grid, dim3(GEMM_T), 0, (hipStream_t)stream, g);
   else
     hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, (hipStream_t)stream, g);
