@@ -32,7 +32,8 @@ constexpr int VG_COPIES = 16;   // copies of each bin's sum in LDS, by lane
 // Bin of a pair at squared distance d2, or -1: the integer that the definition
 // decides in FP64 without fused multiply-add, h = sqrt(d2), 0 < h <= hmax,
 // floor(h / hmax * nbins).  An estimate good to 1e-14 decides it unless it falls
-// within 1e-9 of an integer; only those pairs evaluate the definition itself.
+// within 1e-9 of an integer; only those pairs evaluate the definition itself (and all
+// pairs where hmax is so small that the 1e-300 below shows: scale is a NaN then).
 __device__ __forceinline__ int vg_bin(double d2, double hmax, double scale, int nbins) {
   const double x = d2 + 1e-300;
   const double y = __builtin_amdgcn_rsq(x);
@@ -71,7 +72,7 @@ variogram_pairs_kernel(const double* __restrict__ locs, int64_t locs_stride, con
   for (int q = threadIdx.x; q < per; q += T) scnt[q] = 0u;
   __syncthreads();
   const int copy = threadIdx.x & (VG_COPIES - 1);
-  const double scale = (double)nbins / hmax;
+  const double scale = hmax > 1e-130 ? (double)nbins / hmax : (double)NAN;
   const double* Y[S];
 #pragma unroll
   for (int u = 0; u < S; ++u) Y[u] = y + (size_t)(b0 + u < nsets ? b0 + u : nsets - 1) * y_stride;
