@@ -18,11 +18,12 @@
 // Only 4 x 4 inverses are used (inverses of whole tiles would lose accuracy
 // with the condition of 16 columns).
 //
-// n = 20,000 in 1,500 blocks, m = 450 (p about 463, nu = 3/2): 5.44 ms with one
+// n = 20,000 in 1,500 blocks, m = 450 (p about 463, nu = 3/2): 5.41 ms with one
 // tile column per panel and divisions in the row solves, 1.88 ms now.  Of the time the
-// matrix cores work 43 % and the vector units 17 % (they share their
+// matrix cores work 42 % and the vector units 20 % (they share their
 // cycles); the rest is waiting, mostly at the barriers around the diagonal
-// blocks.  Memory is no bound (2.4 GB read, 1.1 GB written).  Measured and
+// blocks.  5.0 GB are read and 1.2 GB written past the L2, 3.3 TB/s where a copy
+// reaches 4.9.  Measured and
 // not better: three waves per SIMD (2.44 ms, scratch), the panel operands
 // prefetched as the row operands are (2.16), neither prefetched (2.07).
 #include "internal.hpp"

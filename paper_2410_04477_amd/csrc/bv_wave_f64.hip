@@ -8,7 +8,7 @@ namespace bv {
 hipError_t launch_wave_f64(int g, int mode, const AdjArgs& a, const ThetaPack& thp, int grid, hipStream_t s) {
   // Value: from G = 7 on a wave has its SIMD to itself and the kernel that keeps the
   // row solves off the LDS is the faster one (n = 1e6, m = 120, G = 9: 3.74 ms with the
-  // general kernel, 3.42 with it); G = 11 exceeds the registers of both and stays.
+  // general kernel, 3.43 with it); G = 11 exceeds the registers of both and stays.
   if (mode == 0)
     return g >= 7 && g <= 10 ? launch_rows_value(g, a, thp, grid, s) : launch_wave_t<double, 0>(g, a, thp, grid, s);
   if (mode == 1) return launch_wave_f64_tiles(g, a, thp, grid, s);

@@ -486,7 +486,7 @@ __device__ inline void bessel_table(double* tab, const BesselOrder& o, int ln) {
 // operations of the exponentials: 2,000 blocks, m = 30, d l / d range and d l / d nu
 // 1,112 us one distance at a time with its own step (about 110 nodes at
 // x = 1e-4, all weights recomputed, arrays in scratch), 514 us with a rounded
-// exponent (rho off by up to 1e-14), 536 us now.  Outside
+// exponent (rho off by up to 1e-14), 530 us now.  Outside
 // [kBesselLo, kBesselHi] the functions above are called, lane by lane.
 typedef double BesselOut __attribute__((ext_vector_type(8)));
 typedef double Bessel4 __attribute__((ext_vector_type(4)));

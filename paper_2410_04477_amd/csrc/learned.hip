@@ -55,8 +55,9 @@ __device__ __forceinline__ int vg_bin(double d2, double hmax, double scale, int 
 // design (S = 1 where each has its own).  What bounds it: one LDS addition per
 // pair and set; a bin's sum is kept VG_COPIES times, by lane, so that the
 // lanes of a wave meet on few addresses, and the distances are formed once for
-// S sets.  64 sets of 4,096 points: 1,060 us with one copy and one set at a time,
-// 325 so (330 with 32 copies).
+// S sets.  64 sets of 4,096 points: 923 us with one copy and one set at a time,
+// 296 so (no change with 32 copies); two sets 220 and 152 us, although six of the
+// eight sums go unused.
 template <int S, int T>
 __global__ void __launch_bounds__(T)
 variogram_pairs_kernel(const double* __restrict__ locs, int64_t locs_stride, const double* __restrict__ y,
@@ -487,7 +488,9 @@ extern "C" int vecchia_variogram(const double* locs, int64_t locs_stride, const 
   double* ps = static_cast<double*>(workspace);
   unsigned* pc = reinterpret_cast<unsigned*>(ps + (size_t)nsets * nchunks * nbins);
   // eight sets at a time on a shared design (four above 32 bins): at most 36 kB of
-  // LDS, four workgroups of eight waves per compute unit
+  // LDS, four workgroups of eight waves per compute unit.  2 to 16 sets of 4,096
+  // points take 152 us at 32 bins and 109 us at 64, one set 153 us; with one set at a
+  // time 220 to 318 us.
   if (locs_stride == 0 && nsets > 1 && nbins <= 32)
     LCHECK((launch_pairs<8, 512>(locs, 0, y, y_stride, k, nsets, nbins, hmax, nchunks, ps, pc, s)));
   else if (locs_stride == 0 && nsets > 1)

@@ -19,11 +19,11 @@
 // share the same units on gfx950 (a wave that alternates them takes the sum of
 // their times), so a block costs its MFMA time plus its vector instructions,
 // and at one wave per SIMD every wait as well.  FP64, n = 1e6, m = 120: value
-// 4.68 -> 3.73 ms, prediction of 1e5 points 1.12 -> 0.78 ms; n = 1e5, m = 60:
-// value and gradient 761 -> 496 us (square root, exponential and 1 / sqrt in a
-// third-order step from the hardware estimates, masks only in the edge tiles,
-// row panels, two waves per SIMD up to G = 5 or 6).  Lanes exchange panel data through LDS with wavefront-scope
-// fences, so a panel costs no cross-wave synchronisation.  Pivots d_k and
+// 4.68 -> 3.73 ms (3.43 with the kernel of wave_rows.hpp), prediction of 1e5 points
+// 1.12 -> 0.76 ms; n = 1e5, m = 60: value and gradient 757 -> 490 us (square root,
+// exponential and 1 / sqrt from the hardware estimates, masks only in the edge
+// tiles, row panels, two waves per SIMD up to G = 5 or 6).  Lanes exchange panel data
+// through LDS with wavefront-scope fences, so a panel costs no cross-wave synchronisation.  Pivots d_k and
 // border entries w_k (k >= m) give log det and the quadratic form, summed in
 // FP64.
 //
@@ -199,8 +199,9 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   // branches in the generation, the panel kept by columns and one nest of updates.
   // The value at G = 11 and the prediction from G = 10 on (Bessel form: 11) exceed them
   // either way, and spill less so: 3,000 blocks, value at G = 11 610 us by rows
-  // (with 752 bytes of scratch), 464 so (612; 521 before the row panels); prediction at G = 11 766 and 563 us
-  // (1,220 and 868), at G = 10 387 and 325 us (612 and 356), but at G = 9 224 and 256 us.
+  // (with 752 bytes of scratch), 464 so (612; 521 before the row panels); prediction at
+  // G = 11 766 and 563 us (1,220 and 868), at G = 10 387 and 325 us (612 and 356), but
+  // at G = 9 224 and 256 us.
   constexpr bool TIGHT = sizeof(T) == 8 && ((MODE == 5 && G == 9) || ((MODE == 0 || MODE == 4) && G >= (GEN ? 11 : 10)));
   constexpr bool STAGED = wave_min_waves<T, G, MODE, GEN>() == 1;
   T* work = su + 3 * P;

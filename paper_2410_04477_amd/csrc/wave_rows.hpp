@@ -12,12 +12,11 @@
 //
 // What bounds it: one wave per SIMD from G = 6 or 7 on, so every wait shows.  G = 9: a
 // wave lives 154,000 cycles, of which 795 matrix products take 51,000, other vector
-// instructions about as much, and waits (LDS, the gathers, results of the
-// products and of the pivots' chains) the rest; instruction fetch is no matter
-// (150 KB of code, 0.2 % misses).
-// n = 1e6, m = 120 (G = 9), value: 3.74 ms with the general kernel, 3.42 now.
+// instructions 56,000, and waits (LDS, the gathers, results of the products and of
+// the pivots' chains) the rest.
+// n = 1e6, m = 120 (G = 9), value: 3.74 ms with the general kernel, 3.43 now.
 // Simulator, 24 sets of n = 20,000, m = 150 (G = 10): 80.4 ms with the general
-// kernel, 58.1 now (both with part of the tiles in scratch).
+// kernel, 58.8 now (both with part of the tiles in scratch).
 #pragma once
 #include "wave_kernel.hpp"
 
