@@ -578,8 +578,11 @@ __global__ void __launch_bounds__(64, (wave_min_waves<T, G, MODE, GEN>())) bv_wa
   // exchange in each panel's chain of dependent steps.  Products with the inverse add
   // about 10 % to the rounding error of a block; up to G = 3, where that is the largest
   // part of it and a panel has one or two row tiles, each lane substitutes along its row
-  // instead and keeps one of the four results (SUBST; joint sizes to 33: per-block
-  // error 3.8e-14 -> 3.35e-14, value at n = 2,000 17.8 us either way).
+  // instead and keeps one of the four results (SUBST).  Per-block error against 80 bits,
+  // products / substitution: joint sizes to 33 3.8e-14 / 3.35e-14, to 48 4.6e-14 / 4.1e-14
+  // (nu = 1/2, noise gradient: 3.1e-14 / 2.3e-14).  It costs 1 to 8 %: 12,000 blocks of 8
+  // points and 26 neighbours, value 70.6 / 74.3 us, with the gradient 173 / 178,
+  // prediction 59 / 63; at 2,000 points 17.8 us either way.
   constexpr bool ROWPAN = sizeof(T) == 8 && !LEFT && !TIGHT;
   constexpr bool SUBST = G <= 3;
   auto publish_rows = [&](auto Kc_c, int c0) __attribute__((always_inline)) {
